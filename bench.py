@@ -50,7 +50,7 @@ DECODE_CLASSES = ["embed", "rmsnorm", "gemm_qkv", "attn_decode", "gemm_out", "ge
                   "gemm_down", "merge", "gemm_head"]
 FAMILY_NAMES = {
     "gemm": ["shape-generic", "MFMA tile kernel", "weight-streaming kernel", "matrix-vector kernel"],
-    "attn_prefill": ["shape-generic", "flash kernel, LDS key/value tiles", "flash kernel, register operands", ""],
+    "attn_prefill": ["shape-generic", "flash kernel, LDS key/value tiles", "flash kernel, masked last tile", ""],
     "attn_decode": ["shape-generic", "matrix-core split-K kernel", "vector split-K kernel", ""],
 }
 

@@ -1,7 +1,7 @@
 // Causal flash-style prefill attention on the gfx950 matrix cores (bf16 operands, fp32 softmax).
 //
-// One wavefront owns 32 query rows of one (track, sequence, head) and walks the keys in blocks of
-// 32.  Everything is computed transposed so that no operand ever needs a transpose:
+// One wavefront owns 32 query rows of one (track, sequence, head) and walks the keys in tiles of two
+// blocks of 32.  Everything is computed transposed so that no operand ever needs a transpose:
 //
 //   S^T [32 keys x 32 queries] = K_blk [32 x hd] . Q^T          (A = K rows, B = Q rows; both hd-contiguous)
 //   O^T [hd x 32 queries]     += V^T_blk [hd x 32 keys] . P^T   (A = rows of the V^T cache, key-contiguous;
@@ -36,117 +36,8 @@ union pk8 {
   uint32_t u[4];
 };
 
-template <int HD>
-__global__ void __launch_bounds__(256) attn_prefill_mfma_kernel(const pt_attn_args a) {
-  constexpr int KS = HD / 16;   // MFMAs per S^T block
-  constexpr int HB = HD / 32;   // 32-row blocks of O^T
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int l32 = lane & 31, half = lane >> 5;
-  const int qblocks = gridDim.x;
-  const int qb = qblocks - 1 - (int)blockIdx.x;   // heavy (late) query blocks first
-  const int q0 = qb * 128 + wave * 32;
-  if (q0 >= a.S) return;
-  const int head = blockIdx.y;
-  const int t = blockIdx.z / a.B, seq = blockIdx.z - t * a.B;
-  const int kvh = head / (a.H / a.Hkv);
-  const int64_t hidx = t * a.kv_bstride + seq * a.kv_seq_stride + kvh;
-  const bf16_t* K = (const bf16_t*)a.kc + hidx * a.kv_head_elems;
-  const bf16_t* Vt = (const bf16_t*)a.vc + hidx * ((int64_t)HD * a.s_pad);
-  const int64_t row = (int64_t)seq * a.S + q0 + l32;
-  const int64_t qoff = t * a.q_bstride + row * (a.H * HD) + head * HD;
-  const bf16_t* qrow = (const bf16_t*)a.q + qoff;
-
-  bf16x8_t qf[KS];
-#pragma unroll
-  for (int kk = 0; kk < KS; ++kk) qf[kk] = *(const bf16x8_t*)(qrow + kk * 16 + half * 8);
-
-  const int krow = (l32 & ~12) | ((l32 & 4) << 1) | ((l32 & 8) >> 1);   // pi(l32)
-  const bf16_t* kptr = K + (int64_t)krow * HD + half * 8;
-  const bf16_t* vptr = Vt + (int64_t)l32 * a.s_pad + 8 * half;
-  const float scale_log2 = 1.4426950408889634f / sqrtf((float)HD);
-
-  f32x16_t oacc[HB];
-#pragma unroll
-  for (int hb = 0; hb < HB; ++hb)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) oacc[hb][v] = 0.f;
-  float m_run = -INFINITY, l_run = 0.f;
-
-  const int nkb = q0 / 32 + 1;
-  for (int kb = 0; kb < nkb; ++kb) {
-    f32x16_t s;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) s[v] = 0.f;
-    const bf16_t* kp = kptr + (int64_t)kb * 32 * HD;
-#pragma unroll
-    for (int kk = 0; kk < KS; ++kk) {
-      const bf16x8_t kf = *(const bf16x8_t*)(kp + kk * 16);
-      s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[kk], s, 0, 0, 0);
-    }
-    // register v of this lane: key kb*32 + 16*(v/8) + 8*half + v%8, query q0 + l32
-    float mx = -INFINITY;
-    if (kb == nkb - 1) {
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int key_in = 16 * (v >> 3) + 8 * half + (v & 7);
-        s[v] = key_in > l32 ? -INFINITY : s[v] * scale_log2;
-        mx = fmaxf(mx, s[v]);
-      }
-    } else {
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        s[v] *= scale_log2;
-        mx = fmaxf(mx, s[v]);
-      }
-    }
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-    const float m_new = fmaxf(m_run, mx);
-    const float corr = __builtin_amdgcn_exp2f(m_run - m_new);
-    float psum = 0.f;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      s[v] = __builtin_amdgcn_exp2f(s[v] - m_new);
-      psum += s[v];
-    }
-    l_run = l_run * corr + psum;
-    m_run = m_new;
-    if (__any(corr != 1.0f)) {
-#pragma unroll
-      for (int hb = 0; hb < HB; ++hb)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) oacc[hb][v] *= corr;
-    }
-    pk8 pf[2];
-#pragma unroll
-    for (int u = 0; u < 2; ++u)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) pf[u].u[i] = pack_bf16x2(s[8 * u + 2 * i], s[8 * u + 2 * i + 1]);
-    const bf16_t* vp = vptr + kb * 32;
-#pragma unroll
-    for (int hb = 0; hb < HB; ++hb)
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const bf16x8_t vf = *(const bf16x8_t*)(vp + (int64_t)hb * 32 * a.s_pad + 16 * u);
-        oacc[hb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[u].v, oacc[hb], 0, 0, 0);
-      }
-  }
-  const float l = l_run + __shfl_xor(l_run, 32, 64);
-  const float inv = 1.0f / l;
-  bf16_t* orow = (bf16_t*)a.o + qoff;
-#pragma unroll
-  for (int hb = 0; hb < HB; ++hb)
-#pragma unroll
-    for (int vg = 0; vg < 4; ++vg) {
-      uint2 pk;
-      pk.x = pack_bf16x2(oacc[hb][vg * 4 + 0] * inv, oacc[hb][vg * 4 + 1] * inv);
-      pk.y = pack_bf16x2(oacc[hb][vg * 4 + 2] * inv, oacc[hb][vg * 4 + 3] * inv);
-      *(uint2*)(orow + hb * 32 + 8 * vg + 4 * half) = pk;
-    }
-}
-
-
 // ------------------------------------------------------------------------------------------------
-// LDS-tiled variant (prefill lengths that are a multiple of 64).  A workgroup of 4 wavefronts owns 128
+// LDS-tiled kernel.  A workgroup of 4 wavefronts owns 128
 // query rows of one (track, sequence, head); each wavefront 32 of them.  Keys and values are walked in
 // tiles of 64 positions that are staged once per workgroup in LDS (K tile [64][hd], V^T tile [hd][64],
 // 16-byte chunks XOR-swizzled so that 16 lanes reading 16 different rows never share a bank) and read by
@@ -158,7 +49,12 @@ __global__ void __launch_bounds__(256) attn_prefill_mfma_kernel(const pt_attn_ar
 // ------------------------------------------------------------------------------------------------
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
-template <int HD, int PF>   // PF: operand fragments in flight between LDS and the matrix cores
+// TAIL: the length need not be a multiple of 64 (a template argument: the other form has no masks in its loop).  The last key tile then holds cache positions that no token has
+// written: the causal mask drops their scores (for every row that is stored), and their columns of V^T are zeroed on
+// the way into LDS, because their bytes may be anything and 0 * NaN is not 0.  Query rows past the end repeat the last
+// one and are not stored.  The cache holds max_seq rounded up to 64 positions, so the whole tile may be read.
+// PF: operand fragments in flight between LDS and the matrix cores
+template <int HD, int PF, bool TAIL>
 __global__ void __launch_bounds__(256, HD == 64 ? 3 : 2) attn_prefill_lds_kernel(const pt_attn_args a, int nqb) {
   constexpr int KS = HD / 16;          // MFMAs per 32-key block of S^T
   constexpr int HB = HD / 32;          // 32-row blocks of O^T
@@ -251,15 +147,32 @@ __global__ void __launch_bounds__(256, HD == 64 ? 3 : 2) attn_prefill_lds_kernel
     for (int v = 0; v < 16; ++v) oacc[hb][v] = 0.f;
   float m_run = -INFINITY, l_run = 0.f;   // running max of the raw scores, running sum
 
-  const int ntiles = min((qb * 128 + 128), slen) / 64;     // key tiles this workgroup walks
+  const int ntiles = TAIL ? (min(qb * 128 + 128, slen) + 63) / 64 : min((qb * 128 + 128), slen) / 64;   // key tiles this workgroup walks
+  auto park_v = [&](bf16_t* Vn, int tile) {
+    const int left = slen - tile * 64;      // positions of this tile that hold tokens (64 or more: all)
+#pragma unroll
+    for (int i = 0; i < VCH; ++i) {
+      u32x4_t v = v_reg[i];
+      if (TAIL && left < 64) {              // workgroup-uniform
+        const int p0 = ((tid + i * 256) & 7) * 8;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          uint32_t w = v[j];
+          if (p0 + 2 * j >= left) w &= 0xffff0000u;
+          if (p0 + 2 * j + 1 >= left) w &= 0x0000ffffu;
+          v[j] = w;
+        }
+      }
+      *(u32x4_t*)(Vn + v_dst[i]) = v;
+    }
+  };
 #pragma unroll
   for (int i = 0; i < KCH; ++i) k_reg[i] = *(const u32x4_t*)(k_src[i]);
 #pragma unroll
   for (int i = 0; i < VCH; ++i) v_reg[i] = *(const u32x4_t*)(v_src[i]);
 #pragma unroll
   for (int i = 0; i < KCH; ++i) *(u32x4_t*)(Ks + k_dst[i]) = k_reg[i];
-#pragma unroll
-  for (int i = 0; i < VCH; ++i) *(u32x4_t*)(Vs + v_dst[i]) = v_reg[i];
+  park_v(Vs, 0);
   __syncthreads();
 
   for (int kt = 0; kt < ntiles; ++kt) {
@@ -352,12 +265,12 @@ __global__ void __launch_bounds__(256, HD == 64 ? 3 : 2) attn_prefill_lds_kernel
     bf16_t* Vn = Vs + (cur ^ 1) * HD * 64;
 #pragma unroll
     for (int i = 0; i < KCH; ++i) *(u32x4_t*)(Kn + k_dst[i]) = k_reg[i];
-#pragma unroll
-    for (int i = 0; i < VCH; ++i) *(u32x4_t*)(Vn + v_dst[i]) = v_reg[i];
+    park_v(Vn, nxt);
     __syncthreads();
   }
   if (!active) return;
   const float l = l_run + __shfl_xor(l_run, 32, 64);
+  if (TAIL && q0 + l32 >= slen) return;
   const float inv = 1.0f / l;
   bf16_t* orow = (bf16_t*)a.o + qoff;
 #pragma unroll
@@ -632,10 +545,10 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_prefill_pipe_kernel(const pt_
 // the pipelined one, so the plain kernel stays the default.
 int pt_tune_attn_prefill = 0;
 
-template <int HD>
+template <int HD, bool TAIL>
 static int launch_lds(const pt_attn_args& a, hipStream_t s) {
   const int slen_max = a.seq_info ? a.max_plen : a.S;
-  if (pt_tune_attn_prefill == 1) {
+  if (!TAIL && pt_tune_attn_prefill == 1) {
     // software-pipelined kernel: 8 wavefronts (256 queries) per workgroup, four K / V^T stages in LDS
     constexpr int NW = 8, NSTG = 4;
     const int nqb = (slen_max + NW * 32 - 1) / (NW * 32);
@@ -654,7 +567,7 @@ static int launch_lds(const pt_attn_args& a, hipStream_t s) {
   const dim3 grid((unsigned)total);
   const size_t lds = (size_t)2 * (64 * HD + HD * 64) * sizeof(bf16_t);
   {
-    auto kern = attn_prefill_lds_kernel<HD, 4>;
+    auto kern = attn_prefill_lds_kernel<HD, 4, TAIL>;
     PT_SET_MAX_LDS_ONCE(kern, lds);
     hipLaunchKernelGGL(kern, grid, dim3(256), lds, s, a, nqb);
   }
@@ -662,23 +575,27 @@ static int launch_lds(const pt_attn_args& a, hipStream_t s) {
   return 1;
 }
 
+int pt_launch_attn_prefill_masked(const pt_attn_args& a, hipStream_t s) {
+  if (a.dtype != PT_BF16 || a.pos0 != 0 || a.seq_info || a.row_map || a.S < 2) return 0;
+  if ((a.hd != 64 && a.hd != 128) || (a.s_pad & 7)) return 0;
+  if ((a.q_bstride & 7) || (((uintptr_t)a.q | (uintptr_t)a.o | (uintptr_t)a.kc | (uintptr_t)a.vc) & 15)) return 0;
+  return a.hd == 64 ? launch_lds<64, true>(a, s) : launch_lds<128, true>(a, s);
+}
+
 int pt_launch_attn_prefill_mfma(const pt_attn_args& a, hipStream_t s) {
   if (a.dtype != PT_BF16 || a.pos0 != 0) return 0;
   if (a.hd != 64 && a.hd != 128) return 0;
   if (a.seq_info) {   // ragged batch: every padded length is a multiple of 64, which the LDS-tiled kernel walks
     if ((a.s_pad & 7) || (a.q_bstride & 7) || (((uintptr_t)a.q | (uintptr_t)a.o | (uintptr_t)a.kc | (uintptr_t)a.vc) & 15)) return 0;
-    return a.hd == 64 ? launch_lds<64>(a, s) : launch_lds<128>(a, s);
+    return a.hd == 64 ? launch_lds<64, false>(a, s) : launch_lds<128, false>(a, s);
   }
   if (a.S < 32 || a.S % 32) return 0;
   if ((a.q_bstride & 7) || (((uintptr_t)a.q | (uintptr_t)a.o | (uintptr_t)a.kc | (uintptr_t)a.vc) & 15)) return 0;
-  const int64_t z = (int64_t)a.n_tracks * a.B;
-  if (z > 65535 || a.H > 65535) return 0;
-  dim3 grid((unsigned)((a.S + 127) / 128), (unsigned)a.H, (unsigned)z);
-  if (a.S % 64 == 0 && (a.s_pad & 7) == 0) return a.hd == 64 ? launch_lds<64>(a, s) : launch_lds<128>(a, s);
-  if (a.hd == 64)
-    hipLaunchKernelGGL(attn_prefill_mfma_kernel<64>, grid, dim3(256), 0, s, a);
-  else
-    hipLaunchKernelGGL(attn_prefill_mfma_kernel<128>, grid, dim3(256), 0, s, a);
-  PT_HIP_CHECK(hipGetLastError());
-  return 2;
+  if (a.s_pad & 7) return 0;
+  if (a.S % 64 == 0) return a.hd == 64 ? launch_lds<64, false>(a, s) : launch_lds<128, false>(a, s);
+  // A form that read both operands straight from the cache, one row per lane, used to serve these lengths: 222 us
+  // against 81 us for the tiled kernel at 8 tracks x 16 heads x 128, 1056 tokens; 18 against 14 us at 4 x 4 x 16 heads
+  // x 64, 224 tokens; 11.3 against 10.1 us at 96 tokens; equal (4 us) at 32.
+  const int r = pt_launch_attn_prefill_masked(a, s);
+  return r > 0 ? 2 : r;
 }
