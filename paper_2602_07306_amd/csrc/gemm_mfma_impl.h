@@ -368,15 +368,105 @@ __device__ __forceinline__ void gemm_epilogue(const pt_gemm_args& g, f32x16_t (&
     constexpr int QPITCH = TN + 8;   // bf16 elements per staged row of q / k
     constexpr int VPITCH = 32 + 8;   // bf16 elements per staged V^T row (32 positions)
     constexpr bool CAN_STAGE = STAGED && 32 * QPITCH <= STAGE_ELEMS && TN * VPITCH <= STAGE_ELEMS;
-    bool staged_done = false;
     if constexpr (CAN_STAGE) {
-      // Aligned prefill (32-row blocks inside one sequence, positions a multiple of 8): 32 rows at a
-      // time go through the wavefront's LDS patch.  q and k are rotated in registers, staged row-major
-      // and leave as 16-byte row pieces; v is staged transposed and leaves as 16-byte pieces of V^T
-      // rows (8 consecutive positions of one head-dim index).
-      if ((g.row_map ? g.row_blocks != 0 : (g.S & 31) == 0) && (g.pos0 & 7) == 0 && wave_n < g.N) {
-        staged_done = true;
+      // 32 rows at a time go through the wavefront's LDS patch.  Blocks inside one sequence whose positions start at a
+      // multiple of 8 (all of them when the length is a multiple of 32): q and k are rotated in registers, staged
+      // row-major and leave as 16-byte row pieces; v is staged transposed and leaves as 16-byte pieces of V^T rows
+      // (8 consecutive positions of one head-dim index).  Every other block (sequences that end inside it, rows past
+      // the last one, one row per sequence) looks its rows' places up in a small table in the patch: q and k still
+      // leave as 16-byte pieces, v as runs of consecutive positions, 32 lanes along the rows.
+      // What bounds this: latency of single waited loads and scattered 2-byte stores.  One 1000-token prompt of the Mid
+      // model (4 tracks, K = 1024, N = 3072): 98 us a launch with every element handled on its own, 43 us this way;
+      // 128 rows of decode, one per sequence: 75 against 45 us.
+      if (wave_n < g.N) {
         const bool is_qk = wave_n < hq + hk, is_q = wave_n < hq;
+// One 32-row block whose rows may lie in any sequences.  Rows past the last one repeat it and are not stored.
+        auto any_row_block = [&](auto MI_, auto WIDE_, const float (&rsv)[16]) {
+          constexpr int mi = decltype(MI_)::value;
+          constexpr bool W = decltype(WIDE_)::value;
+          constexpr int HD = W ? 128 : 64, HALF = HD / 2, NW = HALF / 32;
+          constexpr int STG = 32 * QPITCH > TN * VPITCH ? 32 * QPITCH : TN * VPITCH;
+          static_assert(STG % 8 == 0 && STG + 32 * 4 <= STAGE_ELEMS, "no room for the row table");
+          int2* rows = (int2*)(stage + STG);            // (sequence, position) of the block's rows
+          const int mrow0 = wave_m + mi * 32;
+          if (lane < 32) {
+            const pt_rowpos rp = gemm_row_pos(g, min(mrow0 + lane, g.M - 1));
+            rows[lane] = make_int2(rp.seq, rp.pos);
+          }
+          // the patch is private to the wavefront, whose LDS operations stay in order; these keep the compiler from
+          // moving reads of one type over writes of another
+          auto in_order = [] { asm volatile("" ::: "memory"); };
+          in_order();
+          if (is_qk) {
+            const float2* tab = (const float2*)g.rope + col_l;
+            bf16_t* st = stage + row_l * QPITCH + col_l;
+            static_for<NW>([&](auto HB_) {                // 16 / NW rows' table entries in flight at a time
+              constexpr int NV = 16 / NW, v0 = decltype(HB_)::value * NV;
+              float2 cs[NV][NW];
+              static_for<NV>([&](auto V_) {
+                constexpr int v = v0 + decltype(V_)::value;
+                const int pos = rows[8 * (v >> 2) + row_l + (v & 3)].y;
+#pragma unroll
+                for (int w = 0; w < NW; ++w) cs[v - v0][w] = tab[(int64_t)pos * HALF + 32 * w];
+              });
+              static_for<NV>([&](auto V_) {
+                constexpr int v = v0 + decltype(V_)::value;
+                constexpr int row_c = 8 * (v >> 2) + (v & 3);
+                const float rsc = rsv[v];
+                static_for<NI>([&](auto NI_) {
+                  constexpr int ni = decltype(NI_)::value;
+                  constexpr int jb = (ni * 32) & (HD - 1);
+                  constexpr int pn = ni + NW < NI ? ni + NW : ni;
+                  if constexpr (jb < HALF) {
+                    const float2 c = cs[v - v0][jb / 32];
+                    const float lo = rsc * acc_elem<AR>(acc[mi][ni], v);
+                    const float hi = rsc * acc_elem<AR>(acc[mi][pn], v);
+                    st[row_c * QPITCH + ni * 32] = f32_to_bf16(lo * c.x - hi * c.y);
+                    st[row_c * QPITCH + ni * 32 + HALF] = f32_to_bf16(hi * c.x + lo * c.y);
+                  }
+                });
+              });
+            });
+            constexpr int LPR = TN / 8, RPI = 64 / LPR;
+            const int c8 = (lane % LPR) * 8, row_t = lane / LPR;
+            const int c = (is_q ? wave_n : wave_n - hq) + c8;
+            in_order();
+            const int head = c / HD, j = c % HD;
+            static_for<32 / RPI>([&](auto IT_) {
+              constexpr int it = decltype(IT_)::value;
+              const int r = it * RPI + row_t;
+              if (mrow0 + r < g.M) {
+                const int2 rp = rows[r];
+                bf16_t* dst = is_q ? (bf16_t*)g.olp + b * g.olp_bstride + (int64_t)(mrow0 + r) * hq + c
+                                   : (bf16_t*)g.kc + (b * g.kv_bstride + rp.x * g.kv_seq_stride + head) * g.kv_head_elems +
+                                         (int64_t)rp.y * HD + j;
+                *(u32x4_t*)dst = *(const u32x4_t*)(stage + r * QPITCH + c8);
+              }
+            });
+          } else {
+            static_for<4>([&](auto VG_) {
+              constexpr int vg = decltype(VG_)::value;
+              static_for<NI>([&](auto NI_) {
+                constexpr int ni = decltype(NI_)::value;
+                uint2 pk;
+                pk.x = pack_bf16x2(rsv[vg * 4 + 0] * acc_elem<AR>(acc[mi][ni], vg * 4 + 0), rsv[vg * 4 + 1] * acc_elem<AR>(acc[mi][ni], vg * 4 + 1));
+                pk.y = pack_bf16x2(rsv[vg * 4 + 2] * acc_elem<AR>(acc[mi][ni], vg * 4 + 2), rsv[vg * 4 + 3] * acc_elem<AR>(acc[mi][ni], vg * 4 + 3));
+                *(uint2*)(stage + (ni * 32 + col_l) * VPITCH + 8 * vg + row_l) = pk;
+              });
+            });
+            in_order();
+            if (mrow0 + col_l < g.M) {
+              const int2 rp = rows[col_l];                // this lane's row
+              const int head0 = (wave_n - hq - hk) / HD;  // the wavefront's columns lie in whole heads, one after the other
+              bf16_t* dst = (bf16_t*)g.vc + (b * g.kv_bstride + rp.x * g.kv_seq_stride + head0) * ((int64_t)HD * g.s_pad) +
+                            (int64_t)(lane >> 5) * g.s_pad + rp.y;
+              const bf16_t* src = stage + (lane >> 5) * VPITCH + col_l;
+#pragma unroll 8
+              for (int it = 0; it < TN / 2; ++it) dst[(int64_t)(it * 2) * g.s_pad] = src[it * 2 * VPITCH];
+            }
+          }
+          in_order();
+        };
         // The head width as a constant: a wavefront owns whole heads (wave_n is a multiple of hd), so which
         // 32-column tiles hold the low halves, and where their partners are, is then known at compile time.
         auto staged_part = [&](auto WIDE_) {
@@ -397,8 +487,8 @@ __device__ __forceinline__ void gemm_epilogue(const pt_gemm_args& g, f32x16_t (&
             }
             static_for<MI>([&](auto MI_) {
               constexpr int mi = decltype(MI_)::value;
-              const int mrow0 = min(wave_m + mi * 32, g.M - 32);
-              const int pos0b = gemm_row_pos(g, mrow0).pos;
+              const int mrow0 = min(wave_m + mi * 32, g.M - 1);
+              const int pos0b = gemm_row_pos(g, mrow0).pos & ~7;   // (other blocks read a valid entry and drop it)
               const float2* rp = tab + (int64_t)(pos0b + row_l) * HALF;
 #pragma unroll
               for (int w = 0; w < NW; ++w) cs_base[mi][w] = rp[32 * w];
@@ -412,7 +502,11 @@ __device__ __forceinline__ void gemm_epilogue(const pt_gemm_args& g, f32x16_t (&
               const int seq = rp0.seq, pos0b = rp0.pos;
               float rsv[16];
               row_scales(mi, rsv);
-              if (is_qk) {
+              const bool aligned = mrow0 + 32 <= g.M && (pos0b & 7) == 0 &&
+                                   (g.row_map ? g.row_blocks != 0 : pos0b - g.pos0 + 32 <= g.S);   // wave-uniform
+              if (!aligned) {
+                any_row_block(MI_, WIDE_, rsv);
+              } else if (is_qk) {
                 float2 cs_cur[NW];
 #pragma unroll
                 for (int w = 0; w < NW; ++w) cs_cur[w] = cs_base[mi][w];
@@ -487,7 +581,7 @@ __device__ __forceinline__ void gemm_epilogue(const pt_gemm_args& g, f32x16_t (&
         else staged_part(std::false_type{});
       }
     }
-    if (!staged_done)
+    if constexpr (!CAN_STAGE)
     static_for<MI>([&](auto MI_) {
       constexpr int mi = decltype(MI_)::value;
       static_for<4>([&](auto VG_) {
