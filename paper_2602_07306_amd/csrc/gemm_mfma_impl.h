@@ -723,8 +723,16 @@ gemm_mfma_kernel(const pt_gemm_args g, int tiles_m, int tiles_n) {
     const int gr = min(n0 + ld_row + i * (NT / CPR), g.N - 1) - n0;
     w_voff[i] = (uint32_t)((gr * g.ldb + ld_ch * 8) * 2);
   }
-  const char* a_base = (const char*)((const bf16_t*)g.A + b * g.a_bstride + (g.a_rows ? 0 : (int64_t)m0 * g.lda));   // wave-uniform
-  const char* w_base = (const char*)((const bf16_t*)g.W + b * g.w_bstride + group * g.w_gstride + (int64_t)n0 * g.ldb);
+  int bt = b, k_off = 0;   // track and first element of the K slice
+  if constexpr (EPI == EPI_STORE_F32) {
+    if (g.k_tracks > 0) {
+      const int slice = b / g.k_tracks;
+      bt = b - slice * g.k_tracks;
+      k_off = slice * g.K;
+    }
+  }
+  const char* a_base = (const char*)((const bf16_t*)g.A + bt * g.a_bstride + k_off + (g.a_rows ? 0 : (int64_t)m0 * g.lda));   // wave-uniform
+  const char* w_base = (const char*)((const bf16_t*)g.W + bt * g.w_bstride + k_off + group * g.w_gstride + (int64_t)n0 * g.ldb);
   auto load_a = [&](int set, int i, int kstep) { a_reg[set][i] = *(const u32x4_t*)(a_base + (size_t)kstep * (BK * 2) + a_voff[i]); };
   auto load_w = [&](int set, int i, int kstep) { w_reg[set][i] = *(const u32x4_t*)(w_base + (size_t)kstep * (BK * 2) + w_voff[i]); };
 

@@ -42,6 +42,24 @@ static bool cfg_fits(const pt_gemm_args& g, int cfg) {
   return true;
 }
 
+// Expected time in us of a GEMM on tile configuration 0 (256 x 256), 4 (128 x 256) or 2 (128 x 128) with its K cut into
+// `slices`.  A launch runs in rounds of one tile per compute unit (two for configuration 2, whose LDS leaves room for
+// a second workgroup: its fills and epilogues hide behind the other's K loop, so they count once).  What bounds a round
+// is the latency of the K loop's loads, hence a fixed part and a part per K step of 64, fitted on one-round launches at
+// K = 1024 and 4096 (4 tracks, 16 to 64 workgroups): 33.8 / 82, 24.4 / 59.6 and 17.9 / 44.3 us.  It orders the
+// three correctly at M = 96 to 4096 of the Mid, Large and one-GPU-share shapes: e.g. 4 tracks x 1024 x 1024 rows,
+// K = 4096: 88 / 65 / 49 us; 8 tracks x 256 x 2048, K = 8192: 172 / 120 / 91; 4 tracks x 1024 x 3072, K = 1024:
+// 40 / 48 / 41; 4 tracks x 4096 x 8192, K = 1024: 271 / 328 / 304.
+static double tile_us(const pt_gemm_args& g, int cfg, int slices) {
+  const int bm = cfg == 0 ? 256 : 128, bn = cfg == 2 ? 128 : 256;
+  const int64_t tiles = (int64_t)((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn) * g.batch * slices;
+  const double steps = (double)g.K / (slices * GM_BK);
+  const double rounds = (double)((tiles + 255) / 256);
+  if (cfg == 0) return rounds * (16.7 + 1.02 * steps);
+  if (cfg == 4) return rounds * (12.4 + 0.735 * steps);
+  return 9.5 + rounds * 0.585 * steps;
+}
+
 // The tile configuration for a problem, or -1 if the family does not cover it (-2: nothing to do).
 static int choose_cfg(const pt_gemm_args& g) {
   if (g.dtype != PT_BF16) return -1;
@@ -54,20 +72,28 @@ static int choose_cfg(const pt_gemm_args& g) {
   if ((g.epi == EPI_STORE_F32 || g.epi == EPI_RESIDUAL) &&
       ((g.ldo & 3) || (g.N & 3) || (g.out_bstride & 3) || (g.res_bstride & 3) || (((uintptr_t)g.out | (uintptr_t)g.res) & 15))) return -1;
   if (g.epi == EPI_SWIGLU && ((g.olp_bstride & 7) || ((uintptr_t)g.olp & 15))) return -1;
-  // measured at the Large, one-GPU-share and Mid shapes: the register-staged 256 x 256 tile (0) is the fastest for
-  // every epilogue; the direct-to-LDS variants (10, 11) stay reachable through the tuning override
-  static const int big[] = {0, 4, 2, -1}, big_qkv[] = {0, 10, 8, 4, 2, -1}, mid[] = {4, 2, -1}, m64[] = {3, 6, -1}, m32[] = {5, 7, -1};
-  const int* cand;
-  // grouped GEMM: the tile height follows the rows of an average group, not the padded total
-  const int m_sel = g.blk_group && g.grp_rows > 0 && g.grp_rows < g.M ? g.grp_rows : g.M;
-  if (m_sel <= 32) cand = m32;
-  else if (m_sel <= 64) cand = m64;
-  else if (m_sel <= 128 || (int64_t)((g.M + 255) / 256) * ((g.N + 255) / 256) * g.batch < 200) cand = mid;
-  else cand = g.epi == EPI_QKV ? big_qkv : big;
   if (pt_tune_gemm_cfg >= 0 && pt_tune_gemm_cfg < GM_NCFG) return cfg_fits(g, pt_tune_gemm_cfg) ? pt_tune_gemm_cfg : -1;
-  for (; *cand >= 0; ++cand)
-    if (cfg_fits(g, *cand)) return *cand;
-  return -1;
+  static const int m64[] = {3, 6, -1}, m32[] = {5, 7, -1}, odd[] = {8, 10, -1};
+  // Grouped GEMM: the largest tile, also where an average group fills a small part of it.  Group sizes scatter, each
+  // tile past a group's first re-reads its weights, and the reads of the weights are the time: 4 tracks x 8 experts of
+  // width 2048 on K = 1024, gate/up and down in us with 96 rows: 89 + 57 (256 x 256) against 104 + 48 (128 x 256),
+  // 160 + 62 (64 x 256) and 170 + 71 (32 x 256); 256 rows: 107 + 58, 107 + 72, 176 + 82, 148 + 77; 512 rows: 104 + 60
+  // against 123 + 72 (128 x 256).
+  if (g.blk_group && cfg_fits(g, 0)) return 0;
+  if (g.M <= 64) {
+    for (const int* c = g.M <= 32 ? m32 : m64; *c >= 0; ++c)
+      if (cfg_fits(g, *c)) return *c;
+    return -1;
+  }
+  int best = -1;
+  double best_us = 1e30;
+  for (int cfg : {0, 4, 2}) {
+    const double us = cfg_fits(g, cfg) ? tile_us(g, cfg, 1) : 1e30;
+    if (us < best_us) { best_us = us; best = cfg; }
+  }
+  for (const int* c = odd; best < 0 && *c >= 0; ++c)   // head widths that only these own whole
+    if (cfg_fits(g, *c)) best = *c;
+  return best;
 }
 
 bool pt_gemm_mfma_covers(const pt_gemm_args& g) { return choose_cfg(g) >= 0; }
@@ -80,6 +106,33 @@ int pt_gemm_mfma_fold_parts(const pt_gemm_args& g) {
   static const bool staged[GM_NCFG] = {true, true, true, false, true, false, false, false, true, true, true, true};
   if (cfg < 0 || !staged[cfg] || g.N % kWaveN[cfg]) return 0;
   return g.N / kWaveN[cfg];
+}
+
+// Residual GEMMs whose tiles leave compute units idle: every K slice is a launch's worth of tiles more, and the kernel
+// that normalises adds the slices to the residual stream (it would run anyway).  The slices cost their traffic, taken at
+// 4 TB/s.  Measured, out + down projection in us without / with slices: Mid (4 tracks, width 1024) 128 rows 17.7 + 44.5
+// / 12.0 + 18.3, 256 rows 17.9 + 44.3 / 18.3 + 20.0; Large (8 x 2048) 96 rows 31.6 + 84.4 / 23.0 + 59.4; one-GPU share
+// (1 x 8192) 128 rows 80.9 + 283 / 41.7 + 102; the normalising kernel takes 1 to 9 us more.
+int pt_gemm_mfma_ksplit(const pt_gemm_args& g) {
+  const int cfg = choose_cfg(g);
+  if (cfg < 0 || g.epi != EPI_RESIDUAL || g.blk_group || !g.sk_part || ((uintptr_t)g.sk_part & 15) || pt_tune_gemm_cfg >= 0) return 1;
+  const double slice_us = (double)g.batch * g.M * g.N * 8.0 / 4e6;   // written and read once
+  double best_us = cfg == 0 || cfg == 4 || cfg == 2 ? tile_us(g, cfg, 1) : 1e30;
+  int best = 1;
+  for (int slices = 2; slices <= 16; slices *= 2) {
+    if (g.K % (slices * 2 * GM_BK) || (int64_t)slices * g.batch * g.M * g.N > g.sk_part_floats) break;
+    const double us = tile_us(g, 2, slices) + slices * slice_us;
+    if (us < 0.9 * best_us) { best_us = us; best = slices; }
+  }
+  return best;
+}
+
+int pt_launch_gemm_mfma_split(const pt_gemm_args& g, int slices, hipStream_t s) {
+  pt_gemm_args p = g;
+  p.epi = EPI_STORE_F32;
+  p.K = g.K / slices; p.k_tracks = g.batch; p.batch = g.batch * slices;
+  p.out = g.sk_part; p.out_bstride = (int64_t)g.M * g.N; p.ldo = g.N;
+  return launch_epi<EPI_STORE_F32>(p, s, 2);
 }
 
 int pt_launch_gemm_mfma(const pt_gemm_args& g, hipStream_t s) {

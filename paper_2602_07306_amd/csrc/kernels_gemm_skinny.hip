@@ -644,6 +644,7 @@ bool pt_gemm_fuses_norm(const pt_gemm_args& g) {
 }
 
 int pt_gemm_skinny_ksplit(const pt_gemm_args& g) {
+  if (g.M > 64 && g.n_groups == 0) return pt_gemm_mfma_ksplit(g);
   if (!skinny_covers(g)) return 0;
   if (g.epi != EPI_RESIDUAL || !g.sk_part || (g.N & 3) || use_gemv(g)) return 1;
   return plan_skinny(g, g.N / 32, 16).ks;
@@ -653,6 +654,10 @@ int pt_gemm_skinny_ksplit(const pt_gemm_args& g) {
 // pt_gemm_skinny_ksplit are left in g.sk_part instead of the finished residual stream.
 int pt_launch_gemm_skinny(const pt_gemm_args& g_in, bool allow_split, hipStream_t s) {
   pt_gemm_args g = g_in;
+  if (g.M > 64 && g.n_groups == 0) {
+    const int slices = allow_split ? pt_gemm_mfma_ksplit(g) : 1;
+    return slices > 1 ? pt_launch_gemm_mfma_split(g, slices, s) : 0;
+  }
   if (g.n_groups > 0) {
     // grouped: one batch entry per (track, group), each with at most grp_max_rows rows
     if (g.grp_max_rows > 64 || !g.grp_count || !g.grp_base || (g.w_gstride & 7)) return 0;

@@ -437,10 +437,10 @@ static int run_gemm(pt_handle* h, const pt_gemm_args& g_in, int cls) {
 }
 
 // Residual GEMM (out = res + A W^T) followed, when gain is given, by the RMSNorm of the new residual stream
-// into `normed`.  In decode the GEMM may split K over workgroups; the kernel that adds the slices also adds the
+// into `normed`.  With few rows the GEMM may split K over workgroups; the kernel that adds the slices also adds the
 // residual and normalises.
 //
-// Prefill (more than 64 rows, MFMA tile kernels on both sides): the norm is folded into the two GEMMs instead.
+// Otherwise, with more than 64 rows (MFMA tile kernels on both sides), the norm is folded into the two GEMMs instead.
 // The residual GEMM's epilogue also stores bf16(h * gain) into `normed` and per-row partial sums of squares;
 // the GEMM that consumes `normed` (`next`: its shape) multiplies its accumulators by the row's 1/rms.
 // A small kernel turns the partial sums into one factor per row.  *folded_parts > 0 tells the caller that
@@ -454,7 +454,8 @@ static int run_residual_gemm_norm(pt_handle* h, const pt_gemm_args& g_in, int cl
   const int64_t rows = g.M;
   int rc;
   *folded_parts = 0;
-  if (h->path == PT_PATH_AUTO && g_fold_rmsnorm && gain && next && g.M > 64 && g.N == g.ldo && pt_gemm_mfma_covers(*next)) {
+  const int slices = h->path == PT_PATH_AUTO && g.N == g.ldo && g.N <= 8192 ? pt_gemm_skinny_ksplit(g) : 1;
+  if (slices <= 1 && h->path == PT_PATH_AUTO && g_fold_rmsnorm && gain && next && g.M > 64 && g.N == g.ldo && pt_gemm_mfma_covers(*next)) {
     const int parts = pt_gemm_mfma_fold_parts(g);
     if (parts > 0 && parts <= (g.N + 63) / 64) {
       g.nf_out = normed; g.nf_out_bstride = rows * g.N;
@@ -469,8 +470,7 @@ static int run_residual_gemm_norm(pt_handle* h, const pt_gemm_args& g_in, int cl
                                    (float*)(h->active->base + h->active->off_rinv), h->stream);
     }
   }
-  if (h->path == PT_PATH_AUTO && g.M <= 64 && g.N == g.ldo && g.N <= 8192 && pt_gemm_skinny_ksplit(g) > 1) {
-    const int slices = pt_gemm_skinny_ksplit(g);
+  if (slices > 1) {
     {
       prof_scope ps(h, cls);
       rc = pt_launch_gemm_skinny(g, true, h->stream);
@@ -718,7 +718,6 @@ static int forward(pt_handle* h, const pt_workspace& w, const int32_t* dev_token
       g.A = abuf; g.a_bstride = rows * d; g.lda = (int32_t)d;
       g.a_rows = ma.perm; g.a_rows_bstride = ma.slots;
       g.blk_group = ma.blk; g.grp_bstride = ma.slots / 64; g.w_gstride = l.expert_elems;
-      g.grp_rows = (int32_t)((rows * c.top_k + c.n_experts - 1) / c.n_experts);
       g.grp_count = ma.cnt + moe_nblk * 64; g.grp_base = ma.cnt + (moe_nblk + 1) * 64; g.grp_info_bstride = (moe_nblk + 2) * 64;
       g.n_groups = c.n_experts; g.grp_max_rows = (int32_t)std::min<int64_t>(rows, 0x7fffffff);
       g.W = wexp; g.w_bstride = w_bstride; g.ldb = (int32_t)d;
@@ -731,7 +730,6 @@ static int forward(pt_handle* h, const pt_workspace& w, const int32_t* dev_token
       memset(&g, 0, sizeof(g));
       g.A = mbuf; g.a_bstride = ma.slots * f; g.lda = (int32_t)f;
       g.blk_group = ma.blk; g.grp_bstride = ma.slots / 64; g.w_gstride = l.expert_elems;
-      g.grp_rows = (int32_t)((rows * c.top_k + c.n_experts - 1) / c.n_experts);
       g.grp_count = ma.cnt + moe_nblk * 64; g.grp_base = ma.cnt + (moe_nblk + 1) * 64; g.grp_info_bstride = (moe_nblk + 2) * 64;
       g.n_groups = c.n_experts; g.grp_max_rows = (int32_t)std::min<int64_t>(rows, 0x7fffffff);
       g.W = wexp + (size_t)(l.wgu_elems * es); g.w_bstride = w_bstride; g.ldb = (int32_t)f;

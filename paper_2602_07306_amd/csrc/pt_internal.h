@@ -215,7 +215,6 @@ struct pt_gemm_args {
   int64_t a_rows_bstride;
   const int32_t* blk_group;
   int64_t grp_bstride, w_gstride;
-  int32_t grp_rows;   // rows an average group holds (a hint for the tile height; 0 = unknown)
   // The same groups as (first row, row count) per group, for the weight-streaming kernel, which takes a whole
   // group per workgroup when no group can hold more than 64 rows (grp_max_rows): group e of track b has
   // grp_count[b * grp_info_bstride + e] rows starting at row grp_base[b * grp_info_bstride + e].
@@ -223,6 +222,9 @@ struct pt_gemm_args {
   const int32_t* grp_base;
   int64_t grp_info_bstride;
   int32_t n_groups, grp_max_rows;
+  // K slices (MFMA tile kernels, EPI_STORE_F32 only): when k_tracks > 0, batch entry b is slice b / k_tracks of track
+  // b % k_tracks; K is the length of one slice and slice s starts at element s * K of every row of A and W.
+  int32_t k_tracks;
 };
 
 enum { PT_SK_PART_FLOATS = 16 << 20 };   // K-slice scratch inside the caller's workspace arena
@@ -237,10 +239,14 @@ int pt_launch_gemm_mfma(const pt_gemm_args& g, hipStream_t s);
 // For a residual GEMM that the MFMA tile kernels would run with an LDS-staged epilogue: the number of column
 // blocks per row whose sums of squares the kernel can emit (nf_parts), else 0.  Shape fields only.
 int pt_gemm_mfma_fold_parts(const pt_gemm_args& g);
+// K slices with which the MFMA tile kernels would run this residual GEMM when the caller adds the slices (1: no split);
+// pt_launch_gemm_mfma_split leaves them in g.sk_part, [slice][batch][M][N] fp32, as the weight-streaming kernel does.
+int pt_gemm_mfma_ksplit(const pt_gemm_args& g);
+int pt_launch_gemm_mfma_split(const pt_gemm_args& g, int slices, hipStream_t s);
 // True if the MFMA tile kernels cover the problem (shape fields only).
 bool pt_gemm_mfma_covers(const pt_gemm_args& g);
 // Weight-streaming kernel for M <= 64 (decode): returns 2, or 3 for its matrix-vector form (M <= 4).  With
-// allow_split a residual GEMM may leave pt_gemm_skinny_ksplit(g) > 1 K slices in g.sk_part
+// allow_split a residual GEMM (of more rows as well: the MFMA tile kernels then, returning 1) may leave pt_gemm_skinny_ksplit(g) > 1 K slices in g.sk_part
 // ([slice][batch][M][N] fp32) instead of writing out = res + product; pt_launch_resnorm adds them up.
 int pt_launch_gemm_skinny(const pt_gemm_args& g, bool allow_split, hipStream_t s);
 int pt_gemm_skinny_ksplit(const pt_gemm_args& g);
