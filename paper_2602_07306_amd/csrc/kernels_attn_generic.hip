@@ -4,9 +4,18 @@
 // is no multiple of 32 go on to the masked form of the flash kernel instead, unless the caller asked for this kernel.
 #include "pt_device.h"
 
-template <typename T>
+__device__ __forceinline__ float4 load4(const float* p) { return *(const float4*)p; }
+__device__ __forceinline__ float4 load4(const bf16_t* p) {
+  const uint2 v = *(const uint2*)p;
+  return make_float4(__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xffff0000u), __uint_as_float(v.y << 16), __uint_as_float(v.y & 0xffff0000u));
+}
+
+// VEC: four elements per load, the loads of a key row (and of 16 keys of V^T) in flight together, and two groups of
+// keys side by side where a head is at most 32 wide (hd % 4 == 0, pointers aligned).  The loop of single loads waits
+// for memory once per key: one row of the Tiny model (32 to 40 keys, head width 32) 8.6 us before, 5.3 now.
+template <typename T, bool VEC>
 __global__ void __launch_bounds__(64) attn_generic_kernel(pt_attn_args a) {
-  __shared__ float qs[256];
+  __shared__ __attribute__((aligned(16))) float qs[256];
   const int lane = threadIdx.x;
   const int m = blockIdx.x, head = blockIdx.y, t = blockIdx.z;
   const int hd = a.hd;
@@ -37,7 +46,17 @@ __global__ void __launch_bounds__(64) attn_generic_kernel(pt_attn_args a) {
     if (key < nkeys) {
       const T* kr = K + (int64_t)key * hd;
       float dot = 0.f;
-      for (int e = 0; e < hd; ++e) dot = fmaf(qs[e], elem<T>::ld(kr + e), dot);
+      if constexpr (VEC) {
+        float4 d = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll 8
+        for (int e = 0; e < hd; e += 4) {
+          const float4 k4 = load4(kr + e), q4 = *(const float4*)(qs + e);
+          d.x = fmaf(q4.x, k4.x, d.x); d.y = fmaf(q4.y, k4.y, d.y); d.z = fmaf(q4.z, k4.z, d.z); d.w = fmaf(q4.w, k4.w, d.w);
+        }
+        dot = (d.x + d.y) + (d.z + d.w);
+      } else {
+        for (int e = 0; e < hd; ++e) dot = fmaf(qs[e], elem<T>::ld(kr + e), dot);
+      }
       s = dot * scale;
     }
     const float mnew = fmaxf(mrun, wave_max(s));
@@ -48,6 +67,26 @@ __global__ void __launch_bounds__(64) attn_generic_kernel(pt_attn_args a) {
     const int nk = min(64, nkeys - base);
 #pragma unroll
     for (int i = 0; i < 4; ++i) acc[i] *= corr;
+    if constexpr (VEC) {
+      const int groups = hd <= 32 ? 2 : 1, e0 = hd <= 32 ? lane & 31 : lane, grp = hd <= 32 ? lane >> 5 : 0;
+#pragma unroll 4
+      for (int k4 = 0; k4 < nk; k4 += 4 * groups) {   // the same trip count in both groups: the shuffles need every lane
+        const int kk = k4 + 4 * grp;                  // at most 60: the 64 positions of a chunk lie inside the cache row
+        const float p0 = __shfl(p, kk, 64), p1 = __shfl(p, kk + 1, 64), p2 = __shfl(p, kk + 2, 64), p3 = __shfl(p, kk + 3, 64);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int e = e0 + 64 * i;
+          if (e < hd) {
+            const float4 v = load4(Vt + (int64_t)e * a.s_pad + base + kk);
+            // positions that no token has written may hold anything, and 0 * NaN is not 0
+            acc[i] = fmaf(p0, kk < nk ? v.x : 0.f, acc[i]);
+            acc[i] = fmaf(p1, kk + 1 < nk ? v.y : 0.f, acc[i]);
+            acc[i] = fmaf(p2, kk + 2 < nk ? v.z : 0.f, acc[i]);
+            acc[i] = fmaf(p3, kk + 3 < nk ? v.w : 0.f, acc[i]);
+          }
+        }
+      }
+    } else
     for (int kk = 0; kk < nk; ++kk) {
       const float pk = __shfl(p, kk, 64);   // executed by the whole wavefront
 #pragma unroll
@@ -59,6 +98,7 @@ __global__ void __launch_bounds__(64) attn_generic_kernel(pt_attn_args a) {
   }
   T* o = (T*)a.o + qoff;
   const float inv = 1.0f / lsum;
+  if (VEC && hd <= 32) acc[0] += __shfl_xor(acc[0], 32, 64);
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int e = lane + 64 * i;
@@ -77,10 +117,14 @@ int pt_launch_attn_generic(const pt_attn_args& a, hipStream_t s) {
   }
   if (a.hd > 256) return pt_set_error(PT_ERR_INVALID_ARGUMENT, "head_dim > 256");
   dim3 grid((unsigned)rows, (unsigned)a.H, (unsigned)a.n_tracks);
-  if (a.dtype == PT_F32)
-    hipLaunchKernelGGL(attn_generic_kernel<float>, grid, dim3(64), 0, s, a);
-  else
-    hipLaunchKernelGGL(attn_generic_kernel<bf16_t>, grid, dim3(64), 0, s, a);
+  const bool vec = !((a.hd | a.s_pad) & 3) && !(a.kv_head_elems & 3) && !(((uintptr_t)a.kc | (uintptr_t)a.vc) & 15);
+  if (a.dtype == PT_F32) {
+    if (vec) hipLaunchKernelGGL((attn_generic_kernel<float, true>), grid, dim3(64), 0, s, a);
+    else hipLaunchKernelGGL((attn_generic_kernel<float, false>), grid, dim3(64), 0, s, a);
+  } else {
+    if (vec) hipLaunchKernelGGL((attn_generic_kernel<bf16_t, true>), grid, dim3(64), 0, s, a);
+    else hipLaunchKernelGGL((attn_generic_kernel<bf16_t, false>), grid, dim3(64), 0, s, a);
+  }
   PT_HIP_CHECK(hipGetLastError());
   return PT_OK;
 }

@@ -1,6 +1,6 @@
 // Shape-generic GEMM with the fused epilogues: any M, N, K (N even), fp32 or bf16 operands, fp32
 // accumulation on the vector ALU.  It serves the fp32 configuration and every shape the MFMA
-// family does not cover; it is written for clarity, not speed.
+// family does not cover.
 #include "pt_epilogue.h"
 
 #define GG_BK 32
@@ -96,9 +96,90 @@ __global__ void __launch_bounds__(256) gemm_generic_kernel(pt_gemm_args g) {
   }
 }
 
+// fp32, few rows: one wavefront per pair of output columns and MR rows, lanes along K.  What bounds these launches is
+// latency: the kernel above walks K in steps of 32 with two barriers each, about 1.1 us a step; here all loads of
+// 256 elements of K are in flight at once and the lanes are folded at the end.  One row of the Tiny model, event to
+// event with 6.3 us of overhead, K = 128 / 512: 9.5 / 24.5 us before, 6.4 / 6.4 now; fp32 at 4 tracks, width 1024: QKV, out,
+// gate/up, down 63 / 52 / 84 / 188 us before, 15 / 8 / 27 / 18 now.
+template <int MR>
+__global__ void __launch_bounds__(256) gemm_rows_kernel(pt_gemm_args g) {
+  const int lane = threadIdx.x & 63;
+  const int p = blockIdx.x * 4 + (threadIdx.x >> 6), m0 = blockIdx.y * MR, b = blockIdx.z;
+  if (p >= g.N >> 1) return;
+  int n0, n1;
+  pair_columns(g, p, &n0, &n1);
+  const float* w0p = (const float*)g.W + b * g.w_bstride + (int64_t)n0 * g.ldb;
+  const float* w1p = (const float*)g.W + b * g.w_bstride + (int64_t)n1 * g.ldb;
+  const float* ap[MR];
+#pragma unroll
+  for (int r = 0; r < MR; ++r) ap[r] = (const float*)g.A + b * g.a_bstride + (int64_t)min(m0 + r, g.M - 1) * g.lda;
+  float acc0[MR], acc1[MR];
+#pragma unroll
+  for (int r = 0; r < MR; ++r) acc0[r] = acc1[r] = 0.f;
+#pragma unroll 2
+  for (int k = lane * 4; k < g.K; k += 256) {
+    const float4 w0 = *(const float4*)(w0p + k), w1 = *(const float4*)(w1p + k);
+#pragma unroll
+    for (int r = 0; r < MR; ++r) {
+      const float4 a = *(const float4*)(ap[r] + k);
+      acc0[r] = fmaf(a.w, w0.w, fmaf(a.z, w0.z, fmaf(a.y, w0.y, fmaf(a.x, w0.x, acc0[r]))));
+      acc1[r] = fmaf(a.w, w1.w, fmaf(a.z, w1.z, fmaf(a.y, w1.y, fmaf(a.x, w1.x, acc1[r]))));
+    }
+  }
+  float lo = 0.f, hi = 0.f;   // lane r finishes row m0 + r
+#pragma unroll
+  for (int r = 0; r < MR; ++r) {
+    const float s0 = wave_sum(acc0[r]), s1 = wave_sum(acc1[r]);
+    if (lane == r) { lo = s0; hi = s1; }
+  }
+  const int m = m0 + lane;
+  if (lane >= MR || m >= g.M) return;
+  switch (g.epi) {
+    case EPI_STORE_F32:
+      epi_store_f32<float>(g, b, m, n0, lo);
+      epi_store_f32<float>(g, b, m, n1, hi);
+      break;
+    case EPI_RESIDUAL:
+      epi_residual<float>(g, b, m, n0, lo);
+      epi_residual<float>(g, b, m, n1, hi);
+      break;
+    case EPI_SWIGLU:
+      epi_swiglu<float>(g, b, m, p, lo, hi);
+      break;
+    case EPI_QKV:
+      if (n0 < (g.H + g.Hkv) * g.hd) {
+        epi_rope_pair<float>(g, b, m, n0, lo, hi);
+      } else {
+        epi_v<float>(g, b, m, n0, lo);
+        epi_v<float>(g, b, m, n1, hi);
+      }
+      break;
+  }
+}
+
+// Its work per workgroup (2 ns + K / 400 ns of the chip) grows with the rows, the other kernel's chain of K steps (44 ns
+// per element of K) does not: Tiny with 192 rows (QKV, K = 128) 16.7 us against 11.4, with 32 rows 7.9 against 10.4;
+// down (K = 512) with 192 rows 11 against 27.
+static bool rows_covers(const pt_gemm_args& g) {
+  const double wgs = (double)((g.N / 2 + 3) / 4) * ((g.M + 3) / 4) * g.batch;
+  if (wgs * (2.0 + g.K / 400.0) >= 44.0 * g.K || g.M > 4 * 65535) return false;
+  return g.dtype == PT_F32 && !g.blk_group && !g.a_rows && !((g.K | g.lda | g.ldb) & 3) &&
+         !((g.a_bstride | g.w_bstride) & 3) && !(((uintptr_t)g.A | (uintptr_t)g.W) & 15);
+}
+
 int pt_launch_gemm_generic(const pt_gemm_args& g, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0 || g.batch <= 0) return PT_OK;
   if (g.N & 1) return pt_set_error(PT_ERR_INVALID_ARGUMENT, "generic GEMM needs an even N");
+  if (rows_covers(g)) {
+    const int mr = g.M == 1 ? 1 : 4;
+    const dim3 rgrid((unsigned)((g.N / 2 + 3) / 4), (unsigned)((g.M + mr - 1) / mr), (unsigned)g.batch);
+    if (mr == 1)
+      hipLaunchKernelGGL(gemm_rows_kernel<1>, rgrid, dim3(256), 0, s, g);
+    else
+      hipLaunchKernelGGL(gemm_rows_kernel<4>, rgrid, dim3(256), 0, s, g);
+    PT_HIP_CHECK(hipGetLastError());
+    return PT_OK;
+  }
   dim3 grid((unsigned)((g.N / 2 + 15) / 16), (unsigned)((g.M + 15) / 16), (unsigned)g.batch);
   if (grid.y > 65535u) return pt_set_error(PT_ERR_INVALID_ARGUMENT, "generic GEMM: M too large");
   if (g.dtype == PT_F32)
