@@ -161,22 +161,25 @@ __global__ void __launch_bounds__(256) attn_decode_kernel(const pt_attn_args a, 
 }
 
 // Combines the splits of one (track, sequence, head): o = sum_s o_s 2^(m_s - M) / sum_s l_s 2^(m_s - M).
+// Bound by latency: lane s fetches the statistics of split s (at most 64 splits), so that the only chain is two
+// cross-lane reductions; the loads of the outputs do not depend on it.
+static_assert(PT_MAX_SPLITS <= 64, "one lane per split");
 __global__ void __launch_bounds__(64) attn_decode_combine_kernel(const pt_attn_args a, int nsplit) {
-  const int head = blockIdx.x;
+  const int head = blockIdx.x, lane = threadIdx.x;
   const int t = blockIdx.y / a.B, seq = blockIdx.y - t * a.B;
   const int hd = a.hd;
   const float* part = a.partials + ((int64_t)blockIdx.y * a.H + head) * nsplit * (hd + 2);
-  float M = -INFINITY;
-  for (int s = 0; s < nsplit; ++s) M = fmaxf(M, part[s * (hd + 2)]);
-  float L = 0.f;
-  for (int s = 0; s < nsplit; ++s) L += part[s * (hd + 2) + 1] * __builtin_amdgcn_exp2f(part[s * (hd + 2)] - M);
-  const float inv = 1.0f / L;
+  const float* mine = part + min(lane, nsplit - 1) * (hd + 2);
+  const float m = mine[0], l = mine[1];
+  const float M = wave_max(m);
+  const float w = lane < nsplit ? __builtin_amdgcn_exp2f(m - M) : 0.f;
+  const float inv = 1.0f / wave_sum(w * l);
   bf16_t* o = (bf16_t*)a.o + t * a.q_bstride + (int64_t)seq * (a.H * hd) + head * hd;
-  for (int e = threadIdx.x; e < hd; e += 64) {
+  for (int e0 = 0; e0 < hd; e0 += 64) {   // hd is 64 or 128
     float acc = 0.f;
-    for (int s = 0; s < nsplit; ++s)
-      acc += part[s * (hd + 2) + 2 + e] * __builtin_amdgcn_exp2f(part[s * (hd + 2)] - M);
-    o[e] = f32_to_bf16(acc * inv);
+#pragma unroll 8
+    for (int s = 0; s < nsplit; ++s) acc += part[s * (hd + 2) + 2 + e0 + lane] * __shfl(w, s, 64);
+    o[e0 + lane] = f32_to_bf16(acc * inv);
   }
 }
 
@@ -209,18 +212,21 @@ typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
 // Tiles of 128 keys: K [128 x hd] (one contiguous piece of the cache) and V^T [hd x 128] are read by the whole
 // workgroup as 16-byte pieces of whole cache lines, held in registers while the previous tile is multiplied,
-// and parked in LDS (two buffers for hd = 128; one for hd = 64, where a third resident workgroup covers the
-// extra barrier; 16-byte chunk c of row r sits at position c ^ swizzle(r)); wavefront w then
+// and parked in LDS (one buffer; 16-byte chunk c of row r sits at position c ^ swizzle(r)); wavefront w then
 // works on keys 32w .. 32w+31 of the tile with fragments read from LDS.
+// Bound by HBM; what keeps it from the streaming rate are the phases of a workgroup without loads in flight (first
+// tile, merge of the wavefronts), which only another resident workgroup covers.  Registers and LDS are therefore
+// held to three workgroups per compute unit at hd = 64 and two at hd = 128.  At hd = 128 a second LDS buffer (128 KB)
+// and 342 registers had left one: 8 tracks x 64 sequences x 2 KV heads, 512 keys 80.5 -> 64.4 us (3.3 -> 4.2 TB/s),
+// 32 sequences x 4096 keys 201.7 -> 190.2 us; at hd = 64, 4 tracks x 1 sequence x 4096 keys 20.1 -> 17.6 us.
 template <int HD>
-__global__ void __launch_bounds__(256) attn_decode_tiled_kernel(const pt_attn_args a, int nsplit, int keys_per_split) {
+__global__ void __launch_bounds__(256, HD == 64 ? 3 : 2) attn_decode_tiled_kernel(const pt_attn_args a, int nsplit, int keys_per_split) {
   constexpr int KS = HD / 16, HB = HD / 32;
   constexpr int KROW = HD * 2;                  // bytes of a key row
   constexpr int KCH = KROW / 16;                // 16-byte chunks per key row
   constexpr int TILE = 128 * KROW;              // bytes of the K tile = bytes of the V^T tile (hd rows x 256 B)
   constexpr int NLD = TILE / 16 / 256;          // 16-byte pieces per thread and operand
-  constexpr int NBUF = HD == 64 ? 1 : 2;        // LDS buffers: one (and three workgroups per CU) or two
-  extern __shared__ __attribute__((aligned(1024))) char smem[];   // 2 buffers x (K tile + V^T tile)
+  extern __shared__ __attribute__((aligned(1024))) char smem[];   // K tile + V^T tile
   float (*red_o)[HD][DEC_GMAX] = (float (*)[HD][DEC_GMAX])smem;   // reuses the tiles after the key loop
   __shared__ float red_m[4][32], red_l[4][32];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -274,8 +280,8 @@ __global__ void __launch_bounds__(256) attn_decode_tiled_kernel(const pt_attn_ar
       vreg[i] = *(const u32x4_t*)(Vt + ((int64_t)vr * a.s_pad + key) * 2);
     }
   };
-  auto park_tile = [&](int buf, int kb) {
-    char* kt = smem + buf * (2 * TILE);
+  auto park_tile = [&](int kb) {
+    char* kt = smem;
     char* vt = kt + TILE;
     const bool tail = kb + 128 > k1;   // workgroup-uniform
 #pragma unroll
@@ -309,13 +315,12 @@ __global__ void __launch_bounds__(256) attn_decode_tiled_kernel(const pt_attn_ar
 
   const int kfr_row = wave * 32 + krow;         // row of the K tile this lane multiplies
   load_tile(k0);
-  park_tile(0, k0);
+  park_tile(k0);
   __syncthreads();
-  int buf = 0;
-  for (int kb = k0; kb < k1; kb += 128, buf ^= (NBUF - 1)) {
+  for (int kb = k0; kb < k1; kb += 128) {
     const bool more = kb + 128 < k1;
     if (more) load_tile(kb + 128);
-    const char* kt = smem + buf * (2 * TILE);
+    const char* kt = smem;
     const char* vt = kt + TILE;
     const int kw = kb + wave * 32;              // first key of this wavefront's block
     if (kw < k1) {                              // wave-uniform
@@ -368,8 +373,8 @@ __global__ void __launch_bounds__(256) attn_decode_tiled_kernel(const pt_attn_ar
           oacc[hb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[u].v, oacc[hb], 0, 0, 0);
         }
     }
-    if (NBUF == 1) __syncthreads();             // one buffer: everybody is done with the tile before it is replaced
-    if (more) park_tile(buf ^ (NBUF - 1), kb + 128);   // two buffers: last read while tile kb - 128 was multiplied
+    __syncthreads();                            // everybody is done with the tile before it is replaced
+    if (more) park_tile(kb + 128);
     __syncthreads();
   }
   // the two half-waves of a query head hold disjoint key subsets with a common running max
@@ -406,7 +411,7 @@ __global__ void __launch_bounds__(256) attn_decode_tiled_kernel(const pt_attn_ar
 
 template <int HD>
 static int launch_gqa(const pt_attn_args& a, dim3 grid, int nsplit, int kps, hipStream_t s) {
-  constexpr int LDS = (HD == 64 ? 1 : 2) * 2 * 128 * HD * 2;
+  constexpr int LDS = 2 * 128 * HD * 2;
   static_assert(LDS >= 4 * HD * DEC_GMAX * 4, "merge buffer must fit the tiles");
   auto kern = attn_decode_tiled_kernel<HD>;
   PT_SET_MAX_LDS_ONCE(kern, LDS);
