@@ -49,12 +49,15 @@ union pk8 {
 // ------------------------------------------------------------------------------------------------
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
-// TAIL: the length need not be a multiple of 64 (a template argument: the other form has no masks in its loop).  The last key tile then holds cache positions that no token has
-// written: the causal mask drops their scores (for every row that is stored), and their columns of V^T are zeroed on
-// the way into LDS, because their bytes may be anything and 0 * NaN is not 0.  Query rows past the end repeat the last
-// one and are not stored.  The cache holds max_seq rounded up to 64 positions, so the whole tile may be read.
-// PF: operand fragments in flight between LDS and the matrix cores
-template <int HD, int PF, bool TAIL>
+// PF: operand fragments in flight between LDS and the matrix cores.
+// TAIL: the length need not be a multiple of 64 (a template argument: the other form has no masks in its loop).  The
+// last key tile then holds cache positions that no token has written: the causal mask drops their scores (for every row
+// that is stored), and their columns of V^T are zeroed on the way into LDS, because their bytes may be anything and
+// 0 * NaN is not 0.  Query rows past the end repeat the last one and are not stored.  The cache holds max_seq rounded
+// up to 64 positions, so the whole tile may be read.
+// PIECES: bf16 numbers that a probability is multiplied with V as.  One rounds it to 8 bits of significand; three hold
+// all 24 of fp32 (each is the rounded remainder of those before it, and the remainders are exact).
+template <int HD, int PF, bool TAIL, int PIECES>
 __global__ void __launch_bounds__(256, HD == 64 ? 3 : 2) attn_prefill_lds_kernel(const pt_attn_args a, int nqb) {
   constexpr int KS = HD / 16;          // MFMAs per 32-key block of S^T
   constexpr int HB = HD / 32;          // 32-row blocks of O^T
@@ -139,6 +142,11 @@ __global__ void __launch_bounds__(256, HD == 64 ? 3 : 2) attn_prefill_lds_kernel
 #pragma unroll
   for (int st = 0; st < 4; ++st) v_fr[st] = l32 * 64 + (((st * 2 + half) ^ vswz(l32)) * 8);
 
+  // order of the value product's steps: with several pieces all blocks of a 16-key step come one after the other, so
+  // that only one step's pieces are held (all four steps' are 48 registers, which do not fit)
+  auto v_hb = [](int i) { return PIECES == 1 ? i / 4 : i % HB; };
+  auto v_st = [](int i) { return PIECES == 1 ? i % 4 : i / HB; };
+
   const float c_log2 = 1.4426950408889634f / sqrtf((float)HD);
   f32x16_t oacc[HB];
 #pragma unroll
@@ -202,7 +210,7 @@ __global__ void __launch_bounds__(256, HD == 64 ? 3 : 2) attn_prefill_lds_kernel
         // the first product takes the constant 0 as its addend: no register zeroing
         s[rb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[i % PF], qf[kk], kk == 0 ? zero16 : s[rb], 0, 0, 0);
         if (i + PF < 2 * KS) fr[i % PF] = *(const bf16x8_t*)(Kc + k_fr[(i + PF) / KS][(i + PF) % KS]);
-        else fr[i % PF] = *(const bf16x8_t*)(Vc + ((i + PF - 2 * KS) / 4) * 32 * 64 + v_fr[(i + PF - 2 * KS) % 4]);   // first V^T fragments: they do not wait for the softmax
+        else fr[i % PF] = *(const bf16x8_t*)(Vc + v_hb(i + PF - 2 * KS) * 32 * 64 + v_fr[v_st(i + PF - 2 * KS)]);   // first V^T fragments: they do not wait for the softmax
         __builtin_amdgcn_sched_barrier(0);
       }
       // register v of block rb: key kt*64 + rb*32 + 16*(v/8) + 8*half + v%8, query q0 + l32
@@ -245,18 +253,33 @@ __global__ void __launch_bounds__(256, HD == 64 ? 3 : 2) attn_prefill_lds_kernel
           psum += s[rb][v];
         }
       l_run += psum;
-      pk8 pf[4];   // 16-key steps: (rb, u) -> rb*2 + u
+      pk8 pf[PIECES][4];   // 16-key steps: (rb, u) -> rb*2 + u
+      auto make_pieces = [&](int st) {
 #pragma unroll
-      for (int st = 0; st < 4; ++st)
+        for (int i = 0; i < 4; ++i) {
+          float p0 = s[st >> 1][8 * (st & 1) + 2 * i], p1 = s[st >> 1][8 * (st & 1) + 2 * i + 1];
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-          pf[st].u[i] = pack_bf16x2(s[st >> 1][8 * (st & 1) + 2 * i], s[st >> 1][8 * (st & 1) + 2 * i + 1]);
+          for (int pc = 0; pc < PIECES; ++pc) {
+            const uint32_t w = pack_bf16x2(p0, p1);
+            pf[pc][st].u[i] = w;
+            p0 -= __uint_as_float(w << 16);
+            p1 -= __uint_as_float(w & 0xffff0000u);
+          }
+        }
+      };
+      if (PIECES == 1) {
+#pragma unroll
+        for (int st = 0; st < 4; ++st) make_pieces(st);
+      }
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int i = 0; i < HB * 4; ++i) {
-        const int hb = i / 4, st = i % 4;
-        oacc[hb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[(i + 2 * KS) % PF], pf[st].v, oacc[hb], 0, 0, 0);
-        if (i + PF < HB * 4) fr[(i + 2 * KS) % PF] = *(const bf16x8_t*)(Vc + ((i + PF) / 4) * 32 * 64 + v_fr[(i + PF) % 4]);
+        const int hb = v_hb(i), st = v_st(i);
+        if (PIECES > 1 && hb == 0) make_pieces(st);
+#pragma unroll
+        for (int pc = PIECES - 1; pc >= 0; --pc)   // smallest first
+          oacc[hb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[(i + 2 * KS) % PF], pf[pc][st].v, oacc[hb], 0, 0, 0);
+        if (i + PF < HB * 4) fr[(i + 2 * KS) % PF] = *(const bf16x8_t*)(Vc + v_hb(i + PF) * 32 * 64 + v_fr[v_st(i + PF)]);
         __builtin_amdgcn_sched_barrier(0);
       }
     }
@@ -545,7 +568,7 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_prefill_pipe_kernel(const pt_
 // the pipelined one, so the plain kernel stays the default.
 int pt_tune_attn_prefill = 0;
 
-template <int HD, bool TAIL>
+template <int HD, bool TAIL, int PIECES = 1>
 static int launch_lds(const pt_attn_args& a, hipStream_t s) {
   const int slen_max = a.seq_info ? a.max_plen : a.S;
   if (!TAIL && pt_tune_attn_prefill == 1) {
@@ -567,7 +590,7 @@ static int launch_lds(const pt_attn_args& a, hipStream_t s) {
   const dim3 grid((unsigned)total);
   const size_t lds = (size_t)2 * (64 * HD + HD * 64) * sizeof(bf16_t);
   {
-    auto kern = attn_prefill_lds_kernel<HD, 4, TAIL>;
+    auto kern = attn_prefill_lds_kernel<HD, 4, TAIL, PIECES>;
     PT_SET_MAX_LDS_ONCE(kern, lds);
     hipLaunchKernelGGL(kern, grid, dim3(256), lds, s, a, nqb);
   }
@@ -579,7 +602,13 @@ int pt_launch_attn_prefill_masked(const pt_attn_args& a, hipStream_t s) {
   if (a.dtype != PT_BF16 || a.pos0 != 0 || a.seq_info || a.row_map || a.S < 2) return 0;
   if ((a.hd != 64 && a.hd != 128) || (a.s_pad & 7)) return 0;
   if ((a.q_bstride & 7) || (((uintptr_t)a.q | (uintptr_t)a.o | (uintptr_t)a.kc | (uintptr_t)a.vc) & 15)) return 0;
-  return a.hd == 64 ? launch_lds<64, true>(a, s) : launch_lds<128, true>(a, s);
+  // Multiples of 32 multiply with probabilities rounded to bf16, as multiples of 64 do.  Every other length multiplies
+  // with the fp32 probabilities, which the shape-generic kernel would use too: rounded, a pass of two Mid layers is off
+  // its 64-bit value by 3.175e-3 instead of 3.133e-3 (33 tokens) and 3.050e-3 instead of 3.042e-3 (500).  The two more
+  // matrix instructions per fragment cost 17 us of a layer at 1000 tokens, 4 tracks, 16 heads x 64 (Mid prefill 3.49
+  // against 3.76 ms; 150 ms on the shape-generic kernel).
+  if (a.S >= 32 && a.S % 32 == 0) return a.hd == 64 ? launch_lds<64, true>(a, s) : launch_lds<128, true>(a, s);
+  return a.hd == 64 ? launch_lds<64, true, 3>(a, s) : launch_lds<128, true, 3>(a, s);
 }
 
 int pt_launch_attn_prefill_mfma(const pt_attn_args& a, hipStream_t s) {
