@@ -35,6 +35,9 @@ SOURCES = [
     "kernels_gemm_mfma_qkv_b.hip",
     "kernels_gemm_mfma_qkv_c.hip",
     "kernels_gemm_mfma_qkv_d.hip",
+    "kernels_gemm_mfma_qkv_rows_a.hip",
+    "kernels_gemm_mfma_qkv_rows_b.hip",
+    "kernels_gemm_mfma_qkv_rows_c.hip",
     "kernels_gemm_skinny.hip",
     "kernels_attn_generic.hip",
     "kernels_attn_prefill_mfma.hip",

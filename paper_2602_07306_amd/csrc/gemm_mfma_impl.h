@@ -359,7 +359,7 @@ __device__ __forceinline__ void gemm_epilogue(const pt_gemm_args& g, f32x16_t (&
           }
         }
     }
-  } else {  // EPI_QKV
+  } else {  // EPI_QKV, EPI_QKV_ROWS
     const int hd = g.hd, half = hd >> 1, hq = g.H * hd, hk = g.Hkv * hd;
     const bool wide = hd == 128;     // partner tile distance (hd/2)/32: 1 for hd 64, 2 for hd 128
     const int hd_sh = wide ? 7 : 6;  // hd is 64 or 128 here: shifts and masks instead of runtime divisions
@@ -369,18 +369,54 @@ __device__ __forceinline__ void gemm_epilogue(const pt_gemm_args& g, f32x16_t (&
     constexpr int VPITCH = 32 + 8;   // bf16 elements per staged V^T row (32 positions)
     constexpr bool CAN_STAGE = STAGED && 32 * QPITCH <= STAGE_ELEMS && TN * VPITCH <= STAGE_ELEMS;
     if constexpr (CAN_STAGE) {
-      // 32 rows at a time go through the wavefront's LDS patch.  Blocks inside one sequence whose positions start at a
-      // multiple of 8 (all of them when the length is a multiple of 32): q and k are rotated in registers, staged
-      // row-major and leave as 16-byte row pieces; v is staged transposed and leaves as 16-byte pieces of V^T rows
-      // (8 consecutive positions of one head-dim index).  Every other block (sequences that end inside it, rows past
-      // the last one, one row per sequence) looks its rows' places up in a small table in the patch: q and k still
-      // leave as 16-byte pieces, v as runs of consecutive positions, 32 lanes along the rows.
+      // 32 rows at a time go through the wavefront's LDS patch: q and k rotated and row-major, to leave as 16-byte row
+      // pieces, v transposed.
+      //
+      // EPI_QKV promises blocks inside one sequence whose positions start at a multiple of 8 (prompts of a multiple of
+      // 32 tokens, padded ragged batches): q and k are rotated in registers, v leaves as 16-byte pieces of V^T rows
+      // (8 consecutive positions of one head-dim index).
+      //
+      // EPI_QKV_ROWS takes rows of any sequences and positions, looked up in a small table in the patch: every row is
+      // rotated by its own entries of the rotary table, and v leaves as runs of consecutive positions, 32 lanes along
+      // the rows, where its block does not happen to be aligned.  Rows past the last one repeat it and are not stored.
       // What bounds this: latency of single waited loads and scattered 2-byte stores.  One 1000-token prompt of the Mid
-      // model (4 tracks, K = 1024, N = 3072): 98 us a launch with every element handled on its own, 43 us this way;
-      // 128 rows of decode, one per sequence: 75 against 45 us.
+      // model (4 tracks, K = 1024, N = 3072): 98 us a launch with every element handled on its own, 44 us this way (41
+      // for the aligned form at 1024 tokens).
+      // The two are separate kernels, chosen at launch: with both in one, the aligned path spilled 26 to 71 scalar
+      // registers.
       if (wave_n < g.N) {
         const bool is_qk = wave_n < hq + hk, is_q = wave_n < hq;
-// One 32-row block whose rows may lie in any sequences.  Rows past the last one repeat it and are not stored.
+        // the block's v, transposed, into the patch
+        auto stage_v = [&](auto MI_, const float (&rsv)[16]) {
+          constexpr int mi = decltype(MI_)::value;
+          static_for<4>([&](auto VG_) {
+            constexpr int vg = decltype(VG_)::value;
+            static_for<NI>([&](auto NI_) {
+              constexpr int ni = decltype(NI_)::value;
+              uint2 pk;
+              pk.x = pack_bf16x2(rsv[vg * 4 + 0] * acc_elem<AR>(acc[mi][ni], vg * 4 + 0), rsv[vg * 4 + 1] * acc_elem<AR>(acc[mi][ni], vg * 4 + 1));
+              pk.y = pack_bf16x2(rsv[vg * 4 + 2] * acc_elem<AR>(acc[mi][ni], vg * 4 + 2), rsv[vg * 4 + 3] * acc_elem<AR>(acc[mi][ni], vg * 4 + 3));
+              *(uint2*)(stage + (ni * 32 + col_l) * VPITCH + 8 * vg + row_l) = pk;
+            });
+          });
+        };
+        // ... and out of it as pieces of 8 consecutive positions from pos0b on
+        auto store_v_pieces = [&](auto WIDE_, int seq, int pos0b) {
+          constexpr int HD = decltype(WIDE_)::value ? 128 : 64;
+          const int p8 = (lane & 3) * 8;
+          // a wavefront's columns lie in whole heads: head and head-dim index of column (lane >> 2)
+          const int c0 = wave_n - hq - hk + (lane >> 2);
+          const int head0 = c0 / HD, j0 = c0 % HD;
+          bf16_t* dst = (bf16_t*)g.vc + (b * g.kv_bstride + seq * g.kv_seq_stride + head0) * ((int64_t)HD * g.s_pad) +
+                        (int64_t)j0 * g.s_pad + pos0b + p8;
+          const bf16_t* src = stage + (lane >> 2) * VPITCH + p8;
+          static_for<TN / 16>([&](auto IT_) {
+            constexpr int it = decltype(IT_)::value;
+            // column it*16 further on: the head-dim rows of V^T are s_pad apart and heads follow one another
+            *(u32x4_t*)(dst + (int64_t)(it * 16) * g.s_pad) = *(const u32x4_t*)(src + it * 16 * VPITCH);
+          });
+        };
+        // one 32-row block whose rows may lie in any sequences
         auto any_row_block = [&](auto MI_, auto WIDE_, const float (&rsv)[16]) {
           constexpr int mi = decltype(MI_)::value;
           constexpr bool W = decltype(WIDE_)::value;
@@ -444,18 +480,13 @@ __device__ __forceinline__ void gemm_epilogue(const pt_gemm_args& g, f32x16_t (&
               }
             });
           } else {
-            static_for<4>([&](auto VG_) {
-              constexpr int vg = decltype(VG_)::value;
-              static_for<NI>([&](auto NI_) {
-                constexpr int ni = decltype(NI_)::value;
-                uint2 pk;
-                pk.x = pack_bf16x2(rsv[vg * 4 + 0] * acc_elem<AR>(acc[mi][ni], vg * 4 + 0), rsv[vg * 4 + 1] * acc_elem<AR>(acc[mi][ni], vg * 4 + 1));
-                pk.y = pack_bf16x2(rsv[vg * 4 + 2] * acc_elem<AR>(acc[mi][ni], vg * 4 + 2), rsv[vg * 4 + 3] * acc_elem<AR>(acc[mi][ni], vg * 4 + 3));
-                *(uint2*)(stage + (ni * 32 + col_l) * VPITCH + 8 * vg + row_l) = pk;
-              });
-            });
+            stage_v(MI_, rsv);
             in_order();
-            if (mrow0 + col_l < g.M) {
+            // the row map of a batch of many sequences promises nothing about a block; uniform rows may be aligned
+            const int2 r0 = rows[0];
+            if (!g.row_map && mrow0 + 32 <= g.M && (r0.y & 7) == 0 && r0.y - g.pos0 + 32 <= g.S) {   // wave-uniform
+              store_v_pieces(WIDE_, __builtin_amdgcn_readfirstlane(r0.x), __builtin_amdgcn_readfirstlane(r0.y));
+            } else if (mrow0 + col_l < g.M) {
               const int2 rp = rows[col_l];                // this lane's row
               const int head0 = (wave_n - hq - hk) / HD;  // the wavefront's columns lie in whole heads, one after the other
               bf16_t* dst = (bf16_t*)g.vc + (b * g.kv_bstride + rp.x * g.kv_seq_stride + head0) * ((int64_t)HD * g.s_pad) +
@@ -487,8 +518,8 @@ __device__ __forceinline__ void gemm_epilogue(const pt_gemm_args& g, f32x16_t (&
             }
             static_for<MI>([&](auto MI_) {
               constexpr int mi = decltype(MI_)::value;
-              const int mrow0 = min(wave_m + mi * 32, g.M - 1);
-              const int pos0b = gemm_row_pos(g, mrow0).pos & ~7;   // (other blocks read a valid entry and drop it)
+              const int mrow0 = min(wave_m + mi * 32, g.M - 32);
+              const int pos0b = gemm_row_pos(g, mrow0).pos;
               const float2* rp = tab + (int64_t)(pos0b + row_l) * HALF;
 #pragma unroll
               for (int w = 0; w < NW; ++w) cs_base[mi][w] = rp[32 * w];
@@ -502,11 +533,7 @@ __device__ __forceinline__ void gemm_epilogue(const pt_gemm_args& g, f32x16_t (&
               const int seq = rp0.seq, pos0b = rp0.pos;
               float rsv[16];
               row_scales(mi, rsv);
-              const bool aligned = mrow0 + 32 <= g.M && (pos0b & 7) == 0 &&
-                                   (g.row_map ? g.row_blocks != 0 : pos0b - g.pos0 + 32 <= g.S);   // wave-uniform
-              if (!aligned) {
-                any_row_block(MI_, WIDE_, rsv);
-              } else if (is_qk) {
+              if (is_qk) {
                 float2 cs_cur[NW];
 #pragma unroll
                 for (int w = 0; w < NW; ++w) cs_cur[w] = cs_base[mi][w];
@@ -551,34 +578,29 @@ __device__ __forceinline__ void gemm_epilogue(const pt_gemm_args& g, f32x16_t (&
                   *(u32x4_t*)(dst + it * RPI * dpitch) = *(const u32x4_t*)(src + it * RPI * QPITCH);
                 });
               } else {
-                static_for<4>([&](auto VG_) {
-                  constexpr int vg = decltype(VG_)::value;
-                  static_for<NI>([&](auto NI_) {
-                    constexpr int ni = decltype(NI_)::value;
-                    uint2 pk;
-                    pk.x = pack_bf16x2(rsv[vg * 4 + 0] * acc_elem<AR>(acc[mi][ni], vg * 4 + 0), rsv[vg * 4 + 1] * acc_elem<AR>(acc[mi][ni], vg * 4 + 1));
-                    pk.y = pack_bf16x2(rsv[vg * 4 + 2] * acc_elem<AR>(acc[mi][ni], vg * 4 + 2), rsv[vg * 4 + 3] * acc_elem<AR>(acc[mi][ni], vg * 4 + 3));
-                    *(uint2*)(stage + (ni * 32 + col_l) * VPITCH + 8 * vg + row_l) = pk;
-                  });
-                });
-                const int p8 = (lane & 3) * 8;
-                // a wavefront's columns lie in whole heads: head and head-dim index of column (lane >> 2)
-                const int c0 = wave_n - hq - hk + (lane >> 2);
-                const int head0 = c0 / HD, j0 = c0 % HD;
-                bf16_t* dst = (bf16_t*)g.vc + (b * g.kv_bstride + seq * g.kv_seq_stride + head0) * ((int64_t)HD * g.s_pad) +
-                              (int64_t)j0 * g.s_pad + pos0b + p8;
-                const bf16_t* src = stage + (lane >> 2) * VPITCH + p8;
-                static_for<TN / 16>([&](auto IT_) {
-                  constexpr int it = decltype(IT_)::value;
-                  // column it*16 further on: the head-dim rows of V^T are s_pad apart and heads follow one another
-                  *(u32x4_t*)(dst + (int64_t)(it * 16) * g.s_pad) = *(const u32x4_t*)(src + it * 16 * VPITCH);
-                });
+                stage_v(MI_, rsv);
+                store_v_pieces(WIDE_, seq, pos0b);
               }
             }
           });
         };
-        if (wide) staged_part(std::true_type{});
-        else staged_part(std::false_type{});
+        auto any_rows = [&](auto WIDE_) {
+          static_for<MI>([&](auto MI_) {
+            constexpr int mi = decltype(MI_)::value;
+            if (wave_m + mi * 32 < g.M) {
+              float rsv[16];
+              row_scales(mi, rsv);
+              any_row_block(MI_, WIDE_, rsv);
+            }
+          });
+        };
+        if constexpr (EPI == EPI_QKV_ROWS) {
+          if (wide) any_rows(std::true_type{});
+          else any_rows(std::false_type{});
+        } else {
+          if (wide) staged_part(std::true_type{});
+          else staged_part(std::false_type{});
+        }
       }
     }
     if constexpr (!CAN_STAGE)
@@ -695,7 +717,7 @@ gemm_mfma_kernel(const pt_gemm_args g, int tiles_m, int tiles_n) {
   // folded RMSNorm, consumer side: one factor per tile row (1/rms of the row, from pt_launch_row_inv_rms).  The
   // load is issued here and parked in LDS only after the K loop, so nothing waits for it.
   __shared__ __attribute__((aligned(16))) float rs_inv[BM];
-  const bool has_rs = (EPI == EPI_QKV || EPI == EPI_SWIGLU) && g.rs_inv != nullptr;
+  const bool has_rs = (EPI == EPI_QKV || EPI == EPI_QKV_ROWS || EPI == EPI_SWIGLU) && g.rs_inv != nullptr;
   static_assert(BM <= NT, "one factor per thread");
   float rs_mine = 1.0f;
   if (has_rs) rs_mine = g.rs_inv[b * g.rs_bstride + min(m0 + min(tid, BM - 1), g.M - 1)];   // wave-uniform branch
@@ -916,7 +938,7 @@ gemm_dl_kernel(const pt_gemm_args g, int tiles_m, int tiles_n) {
   // folded RMSNorm, consumer side: one factor per tile row (1/rms of the row, from pt_launch_row_inv_rms).  The
   // load is issued here and parked in LDS only after the K loop, so nothing waits for it.
   __shared__ __attribute__((aligned(16))) float rs_inv[BM];
-  const bool has_rs = (EPI == EPI_QKV || EPI == EPI_SWIGLU) && g.rs_inv != nullptr;
+  const bool has_rs = (EPI == EPI_QKV || EPI == EPI_QKV_ROWS || EPI == EPI_SWIGLU) && g.rs_inv != nullptr;
   static_assert(BM <= (NW * 64), "one factor per thread");
   float rs_mine = 1.0f;
   if (has_rs) rs_mine = g.rs_inv[b * g.rs_bstride + min(m0 + min(tid, BM - 1), g.M - 1)];   // wave-uniform branch

@@ -1,5 +1,5 @@
 // Chooses the tile configuration of the MFMA GEMM family by shape and dispatches to the kernels, which are
-// instantiated per epilogue in kernels_gemm_mfma_{store,residual,swiglu,qkv_a..d}.hip from gemm_mfma_impl.h.
+// instantiated per epilogue in kernels_gemm_mfma_{store,residual,swiglu,qkv_a..d,qkv_rows_a..c}.hip from gemm_mfma_impl.h.
 #include "pt_device.h"
 
 template <int EPI, int CFG>
@@ -135,6 +135,23 @@ int pt_launch_gemm_mfma_split(const pt_gemm_args& g, int slices, hipStream_t s) 
   return launch_epi<EPI_STORE_F32>(p, s, 2);
 }
 
+// The tile kernels with an LDS-staged QKV epilogue assume 32-row blocks inside one sequence at positions from a multiple
+// of 8 on; any other rows run the form that looks up every row's place.
+static int launch_qkv(const pt_gemm_args& g, hipStream_t s, int cfg) {
+  if ((g.row_map ? g.row_blocks != 0 : (g.S & 31) == 0) && (g.pos0 & 7) == 0) return launch_epi<EPI_QKV>(g, s, cfg);
+  switch (cfg) {
+    case 0: return pt_gemm_mfma_launch_one<EPI_QKV_ROWS, 0>(g, s);
+    case 1: return pt_gemm_mfma_launch_one<EPI_QKV_ROWS, 1>(g, s);
+    case 2: return pt_gemm_mfma_launch_one<EPI_QKV_ROWS, 2>(g, s);
+    case 4: return pt_gemm_mfma_launch_one<EPI_QKV_ROWS, 4>(g, s);
+    case 8: return pt_gemm_mfma_launch_one<EPI_QKV_ROWS, 8>(g, s);
+    case 9: return pt_gemm_mfma_launch_one<EPI_QKV_ROWS, 9>(g, s);
+    case 10: return pt_gemm_mfma_launch_one<EPI_QKV_ROWS, 10>(g, s);
+    case 11: return pt_gemm_mfma_launch_one<EPI_QKV_ROWS, 11>(g, s);
+    default: return launch_epi<EPI_QKV>(g, s, cfg);   // tiles without a staged epilogue: one form for all rows
+  }
+}
+
 int pt_launch_gemm_mfma(const pt_gemm_args& g, hipStream_t s) {
   const int cfg = choose_cfg(g);
   if (cfg == -2) return 1;
@@ -145,7 +162,7 @@ int pt_launch_gemm_mfma(const pt_gemm_args& g, hipStream_t s) {
     case EPI_STORE_F32: return launch_epi<EPI_STORE_F32>(g, s, cfg);
     case EPI_RESIDUAL: return launch_epi<EPI_RESIDUAL>(g, s, cfg);
     case EPI_SWIGLU: return launch_epi<EPI_SWIGLU>(g, s, cfg);
-    case EPI_QKV: return launch_epi<EPI_QKV>(g, s, cfg);
+    case EPI_QKV: return launch_qkv(g, s, cfg);
   }
   return 0;
 }

@@ -152,6 +152,8 @@ void pt_layout_workspace(const pt_config* c, const pt_layout* l, int64_t rows, i
 // for b < batch (the track dimension), followed by one of the fused epilogues.
 // ---------------------------------------------------------------------------------------------
 enum { EPI_STORE_F32 = 0, EPI_RESIDUAL = 1, EPI_SWIGLU = 2, EPI_QKV = 3 };
+// Inside the MFMA tile kernels: the form of EPI_QKV whose 32-row blocks may hold rows of any sequences and positions.
+enum { EPI_QKV_ROWS = 4 };
 
 struct pt_gemm_args {
   const void* A;

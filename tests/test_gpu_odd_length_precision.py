@@ -1,6 +1,7 @@
 """GPU: what a prompt keeps in 32 bits when its length is no multiple of 32, compared with the shape-generic kernels, which
-hold probabilities in fp32.  The model is one layer whose output projection is
-the identity and whose feed-forward network adds nothing, so the hidden states minus the input are the attention output."""
+hold probabilities in fp32 and read the rotary table at every position.  The model is one layer whose output projection
+is the identity and whose feed-forward network adds nothing, so the hidden states minus the input are the attention
+output."""
 import numpy as np
 import pytest
 
@@ -45,3 +46,25 @@ def test_probabilities_stay_in_32_bits(hd, heads, kv_heads, B, S):
     # by up to 2^-9 of itself and with it nearly every rounding: about 2e-3.
     err = np.linalg.norm(out[0] - out[1]) / np.linalg.norm(out[1])
     assert err < 3e-4, err
+
+
+@pytest.mark.parametrize("hd,heads,kv_heads", [(64, 4, 4), (128, 2, 2)])
+@pytest.mark.parametrize("B,S", [(5, 31), (3, 100), (1, 1000)])
+def test_keys_are_rotated_by_the_table(hd, heads, kv_heads, B, S):
+    d = heads * hd
+    # every projected element is one product, and the upper half of a head is zero: a rotated key is a single product
+    # with the table's cosine or sine, so that every kernel that reads the table leaves the same bytes in the cache
+    half = np.tile(np.concatenate([np.ones(hd // 2), np.zeros(hd // 2)]), kv_heads).astype(np.float32)
+    PB, model = one_layer(hd, heads, kv_heads, B, S, np.eye(d, dtype=np.float32), np.diag(half), np.eye(d, dtype=np.float32))
+    x = torch.from_numpy(np.random.default_rng(S).standard_normal((B, S, d)).astype(np.float32)).cuda()
+    cache = []
+    for path in (PB.PT_PATH_AUTO, PB.PT_PATH_GENERIC):
+        model.pt_set_kernel_path(path)
+        model._kv.zero_()
+        model.pt_prefill(hidden_in=x, logits_mode=PB.PT_LOGITS_NONE)
+        torch.cuda.synchronize()
+        cache.append(model._kv.clone())
+    model.close()
+    assert bool((cache[1] != 0).any())
+    differing = int((cache[0] != cache[1]).sum())
+    assert differing == 0, differing
