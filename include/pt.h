@@ -257,9 +257,7 @@ int pt_profile_reset(pt_handle* h);
  *   GEMM classes       1 = MFMA tile kernel (more than 64 rows), 2 = weight-streaming kernel
  *                      (5..64 rows), 3 = matrix-vector kernel (1..4 rows)
  *   PT_K_ATTN_PREFILL  1 = flash-style kernel with LDS key/value tiles, 2 = its form with
- *                      a masked last tile (lengths that are a multiple of 32 but not of 64);
- *                      family 0 counts every other length, which PT_PATH_AUTO serves with the
- *                      masked form too where dtype and head_dim allow
+ *                      a masked last tile (lengths that are no multiple of 64)
  *   PT_K_ATTN_DECODE   1 = matrix-core split-K kernel (up to 32 query heads per KV head),
  *                      2 = vector split-K kernel (larger groups)
  * counts receives PT_FAMILY_COUNT values. */

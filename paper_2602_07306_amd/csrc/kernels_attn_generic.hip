@@ -1,7 +1,6 @@
 // Shape-generic causal attention over the KV cache (prefill and decode), one wavefront per
 // (query row, head): online softmax over chunks of 64 keys, fp32 arithmetic on the vector ALU.
-// Serves the fp32 configuration and the shapes the tuned attention kernels do not cover.  Prompts in bf16 whose length
-// is no multiple of 32 go on to the masked form of the flash kernel instead, unless the caller asked for this kernel.
+// Serves the fp32 configuration and the shapes the tuned attention kernels do not cover.
 #include "pt_device.h"
 
 __device__ __forceinline__ float4 load4(const float* p) { return *(const float4*)p; }
@@ -109,12 +108,6 @@ __global__ void __launch_bounds__(64) attn_generic_kernel(pt_attn_args a) {
 int pt_launch_attn_generic(const pt_attn_args& a, hipStream_t s) {
   const int64_t rows = a.seq_info ? a.rows : (int64_t)a.B * a.S;
   if (rows <= 0) return PT_OK;
-  if (a.any_length) {
-    // one key row per lane and one value column per step, nothing shared between query rows: 9.1 ms a layer for one
-    // prompt of 1000 tokens (4 tracks, 16 heads x 64), against 0.04 ms for the matrix-core form
-    const int r = pt_launch_attn_prefill_masked(a, s);
-    if (r != 0) return r < 0 ? r : PT_OK;
-  }
   if (a.hd > 256) return pt_set_error(PT_ERR_INVALID_ARGUMENT, "head_dim > 256");
   dim3 grid((unsigned)rows, (unsigned)a.H, (unsigned)a.n_tracks);
   const bool vec = !((a.hd | a.s_pad) & 3) && !(a.kv_head_elems & 3) && !(((uintptr_t)a.kc | (uintptr_t)a.vc) & 15);

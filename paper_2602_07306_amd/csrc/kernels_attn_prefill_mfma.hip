@@ -598,33 +598,23 @@ static int launch_lds(const pt_attn_args& a, hipStream_t s) {
   return 1;
 }
 
-int pt_launch_attn_prefill_masked(const pt_attn_args& a, hipStream_t s) {
-  if (a.dtype != PT_BF16 || a.pos0 != 0 || a.seq_info || a.row_map || a.S < 2) return 0;
-  if ((a.hd != 64 && a.hd != 128) || (a.s_pad & 7)) return 0;
-  if ((a.q_bstride & 7) || (((uintptr_t)a.q | (uintptr_t)a.o | (uintptr_t)a.kc | (uintptr_t)a.vc) & 15)) return 0;
-  // Multiples of 32 multiply with probabilities rounded to bf16, as multiples of 64 do.  Every other length multiplies
-  // with the fp32 probabilities, which the shape-generic kernel would use too: rounded, a pass of two Mid layers is off
-  // its 64-bit value by 3.175e-3 instead of 3.133e-3 (33 tokens) and 3.050e-3 instead of 3.042e-3 (500).  The two more
-  // matrix instructions per fragment cost 17 us of a layer at 1000 tokens, 4 tracks, 16 heads x 64 (Mid prefill 3.49
-  // against 3.76 ms; 150 ms on the shape-generic kernel).
-  if (a.S >= 32 && a.S % 32 == 0) return a.hd == 64 ? launch_lds<64, true>(a, s) : launch_lds<128, true>(a, s);
-  return a.hd == 64 ? launch_lds<64, true, 3>(a, s) : launch_lds<128, true, 3>(a, s);
-}
-
 int pt_launch_attn_prefill_mfma(const pt_attn_args& a, hipStream_t s) {
   if (a.dtype != PT_BF16 || a.pos0 != 0) return 0;
   if (a.hd != 64 && a.hd != 128) return 0;
-  if (a.seq_info) {   // ragged batch: every padded length is a multiple of 64, which the LDS-tiled kernel walks
-    if ((a.s_pad & 7) || (a.q_bstride & 7) || (((uintptr_t)a.q | (uintptr_t)a.o | (uintptr_t)a.kc | (uintptr_t)a.vc) & 15)) return 0;
+  if ((a.s_pad & 7) || (a.q_bstride & 7) || (((uintptr_t)a.q | (uintptr_t)a.o | (uintptr_t)a.kc | (uintptr_t)a.vc) & 15)) return 0;
+  if (a.seq_info)   // ragged batch: every padded length is a multiple of 64
     return a.hd == 64 ? launch_lds<64, false>(a, s) : launch_lds<128, false>(a, s);
-  }
-  if (a.S < 32 || a.S % 32) return 0;
-  if ((a.q_bstride & 7) || (((uintptr_t)a.q | (uintptr_t)a.o | (uintptr_t)a.kc | (uintptr_t)a.vc) & 15)) return 0;
-  if (a.s_pad & 7) return 0;
+  if (a.S < 2) return 0;
   if (a.S % 64 == 0) return a.hd == 64 ? launch_lds<64, false>(a, s) : launch_lds<128, false>(a, s);
-  // A form that read both operands straight from the cache, one row per lane, used to serve these lengths: 222 us
-  // against 81 us for the tiled kernel at 8 tracks x 16 heads x 128, 1056 tokens; 18 against 14 us at 4 x 4 x 16 heads
-  // x 64, 224 tokens; 11.3 against 10.1 us at 96 tokens; equal (4 us) at 32.
-  const int r = pt_launch_attn_prefill_masked(a, s);
+  // The other lengths mask the last key tile.  Multiples of 32 multiply with probabilities rounded to bf16, as multiples
+  // of 64 do (a form that read both operands straight from the cache, one row per lane, used to serve them: 222 us
+  // against 81 us at 8 tracks x 16 heads x 128, 1056 tokens; 18 against 14 us at 4 x 4 x 16 heads x 64, 224 tokens;
+  // 11.3 against 10.1 us at 96 tokens; equal (4 us) at 32).  All others multiply with the fp32 probabilities, which the
+  // shape-generic kernel would use too: rounded, a pass of two Mid layers is off its 64-bit value by 3.175e-3 instead of
+  // 3.133e-3 (33 tokens) and 3.050e-3 instead of 3.042e-3 (500).  One prompt of 1000 tokens, 4 tracks x 16 heads x 64:
+  // 46 us a launch (31 with rounded probabilities), 9.1 ms on the shape-generic kernel.
+  int r;
+  if (a.S % 32 == 0) r = a.hd == 64 ? launch_lds<64, true>(a, s) : launch_lds<128, true>(a, s);
+  else r = a.hd == 64 ? launch_lds<64, true, 3>(a, s) : launch_lds<128, true, 3>(a, s);
   return r > 0 ? 2 : r;
 }

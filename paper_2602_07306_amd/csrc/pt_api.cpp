@@ -669,7 +669,6 @@ static int forward(pt_handle* h, const pt_workspace& w, const int32_t* dev_token
     a.H = c.n_heads; a.Hkv = c.n_kv_heads; a.hd = c.head_dim; a.s_pad = (int32_t)l.s_pad;
     a.dtype = c.dtype;
     a.partials = (float*)(w.base + w.off_part); a.max_splits = w.max_splits;
-    a.any_length = h->path == PT_PATH_AUTO;
     if (rg) {
       a.row_map = rg->row_map; a.seq_info = ragged_prefill ? rg->seq_info : nullptr;
       a.max_pos = rg->max_pos; a.max_plen = rg->max_plen; a.rows = rows;

@@ -280,15 +280,10 @@ struct pt_attn_args {
   const int4* seq_info;
   int32_t max_pos, max_plen;
   int64_t rows;
-  // pt_launch_attn_generic may hand the problem to the matrix-core kernel for prompts of any length
-  int32_t any_length;
 };
 
 int pt_launch_attn_generic(const pt_attn_args& a, hipStream_t s);
 int pt_launch_attn_prefill_mfma(const pt_attn_args& a, hipStream_t s);  // 1: LDS-tiled, 2: with a masked last tile
-// The LDS-tiled kernel with a masked last key tile, for a uniform prefill of any length; 0 if it does not cover the
-// problem, 1 when launched.
-int pt_launch_attn_prefill_masked(const pt_attn_args& a, hipStream_t s);
 int pt_launch_attn_decode(const pt_attn_args& a, hipStream_t s);        // 1: matrix-core kernel, 2: vector kernel
 
 // Tuning overrides (pt_set_tuning): tile configuration of the MFMA GEMM (-1 = by shape) and plan of the

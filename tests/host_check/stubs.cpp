@@ -150,9 +150,9 @@ int pt_launch_gemm_skinny(const pt_gemm_args& g_in, bool allow_split, hipStream_
 // ------------------------------------------------------------------------------------------------ attention
 int pt_launch_attn_generic(const pt_attn_args& a, hipStream_t) { check_attn(a); return PT_OK; }
 int pt_launch_attn_prefill_mfma(const pt_attn_args& a, hipStream_t) {
-  if (g_mode == 0 || a.dtype != PT_BF16 || (a.hd != 64 && a.hd != 128) || a.S % 32) return 0;
+  if (g_mode == 0 || a.dtype != PT_BF16 || (a.hd != 64 && a.hd != 128) || a.S < 2) return 0;
   check_attn(a);
-  return 1;
+  return a.S % 64 && !a.seq_info ? 2 : 1;
 }
 int pt_launch_attn_decode(const pt_attn_args& a, hipStream_t) {
   if (g_mode == 0 || a.dtype != PT_BF16 || (a.hd != 64 && a.hd != 128)) return 0;

@@ -5,7 +5,7 @@ import pytest
 
 from oracle import pt_oracle as O
 from paper_2602_07306_amd import inputs as I
-from tests.helpers import BF16_TOL, assert_close, oracle_prefill, small_bf16_config
+from tests.helpers import BF16_TOL, assert_close, oracle_prefill, path_counts, small_bf16_config
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -24,8 +24,11 @@ def test_prefill_of_any_length_ignores_unwritten_cache(hd, heads, kv_heads, B, S
     model = PB.PTModel(cfg)
     model.pt_init_weights(21)
     model._kv.fill_(255)   # bf16 NaN everywhere
+    model.pt_profile_reset()
     lg, hid = model.pt_prefill(torch.from_numpy(tokens).cuda(), logits_mode=PB.PT_LOGITS_ALL, want_hidden=True)
     torch.cuda.synchronize()
+    counts = path_counts(model)["attn_prefill"]   # the masked form unless the last tile is full, never the generic kernel
+    assert counts[1 if S % 64 == 0 else 2] == cfg.n_layers and sum(counts) == cfg.n_layers, counts
     assert_close(lg.cpu().numpy().reshape(B, S, -1), ref["logits"], BF16_TOL, "prefill logits")
     assert_close(hid.cpu().numpy(), ref["hidden"], BF16_TOL, "prefill hidden")
     step, _, _ = model.pt_decode_step(torch.from_numpy(nxt).cuda())

@@ -63,9 +63,9 @@ def run_case(cfg, seed, B, S, steps, paths):
 
 
 def check_kernel_families(cfg, S, steps, counts):
-    """Which kernels served the two legs.  The forced leg must have launched shape-generic kernels only.  The
-    automatic leg must not have fallen back to them, except for the one documented reason among these cases:
-    prefill attention needs a prompt length that is a multiple of 32 (a one-token prompt runs the decode kernel)."""
+    """Which kernels served the two legs.  The forced leg must have launched shape-generic kernels only, the automatic
+    leg none of them; its prefill attention masks the last key tile of lengths that are no multiple of 64 (a one-token
+    prompt runs the decode kernel)."""
     from paper_2602_07306_amd import binding as PB
     L = cfg.n_layers
     pre, dec = counts[PB.PT_PATH_GENERIC]
@@ -74,13 +74,14 @@ def check_kernel_families(cfg, S, steps, counts):
             assert sum(leg[c][1:]) == 0, (c, leg[c])
     assert pre["gemm_qkv"][0] == L and dec["gemm_qkv"][0] == L * steps
     pre, dec = counts[PB.PT_PATH_AUTO]
-    attn_generic = S != 1 and (S % 32 != 0 or S < 32)
     for c in GEMM_CLASSES:
         assert pre[c][0] == 0 and dec[c][0] == 0, ("fell back to the generic GEMM", c, pre[c], dec[c])
         expect = 1 if c == "gemm_head" else L
         assert sum(pre[c]) == expect and sum(dec[c]) == expect * steps, (c, pre[c], dec[c])
     pre_attn = pre["attn_decode"] if S == 1 else pre["attn_prefill"]
-    assert pre_attn[0] == (L if attn_generic else 0) and sum(pre_attn) == L, pre_attn
+    assert pre_attn[0] == 0 and sum(pre_attn) == L, pre_attn
+    if S != 1:
+        assert pre_attn[1 if S % 64 == 0 else 2] == L, pre_attn
     assert dec["attn_decode"][0] == 0 and sum(dec["attn_decode"]) == L * steps, dec["attn_decode"]
     return pre, dec
 
@@ -91,7 +92,7 @@ CASES = {
     "hd128": (dict(head_dim=128, n_heads=2, n_kv_heads=2), 2, 128, 2),
     "gqa_hd64": (dict(n_kv_heads=2), 2, 96, 2),
     "gqa_1kv_hd128": (dict(head_dim=128, n_heads=4, n_kv_heads=1, d_model=512), 1, 160, 2),
-    "ragged_rows": (dict(), 2, 100, 2),                  # S not a multiple of any tile: M tail, generic attention
+    "ragged_rows": (dict(), 2, 100, 2),                  # S not a multiple of any tile: M tail, masked attention tile
     "three_tracks": (dict(n_tracks=3, n_layers=3, block_depth=1, merge_scale=1.0 / 3), 1, 64, 1),
     "split_decode": (dict(max_batch=1, max_seq=1024), 1, 704, 3),   # decode context split in two, ragged tail
     "one_token_prompt": (dict(), 2, 1, 3),
@@ -152,7 +153,7 @@ def test_small_bf16_models_match_the_oracle(name):
     if name in ("gqa_24_per_group", "gqa_16_per_group", "split_decode", "gqa_split_decode"):
         assert dec["attn_decode"][1] == L * steps
     if name == "gqa_hd64":
-        assert pre["attn_prefill"][2] == L          # 96 tokens: the register-operand flash kernel
+        assert pre["attn_prefill"][2] == L          # 96 tokens: the flash kernel with a masked last tile
     if name in ("hd64_tiles", "hd128", "long_prompt_hd64", "long_prompt_hd128_gqa"):
         assert pre["attn_prefill"][1] == L          # the LDS-tiled flash kernel
 
