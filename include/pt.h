@@ -260,6 +260,8 @@ int pt_profile_reset(pt_handle* h);
  *                      a masked last tile (lengths that are no multiple of 64)
  *   PT_K_ATTN_DECODE   1 = matrix-core split-K kernel (up to 32 query heads per KV head),
  *                      2 = vector split-K kernel (larger groups)
+ *   PT_K_RMSNORM       1 = the kernel that adds the K slices of a residual GEMM (once for every
+ *                      sliced GEMM; the other launches of this class are not counted)
  * counts receives PT_FAMILY_COUNT values. */
 enum { PT_FAMILY_GENERIC = 0, PT_FAMILY_COUNT = 4 };
 int pt_profile_paths(pt_handle* h, int32_t kernel_class, int64_t* counts);

@@ -128,11 +128,7 @@ int pt_gemm_mfma_ksplit(const pt_gemm_args& g) {
 }
 
 int pt_launch_gemm_mfma_split(const pt_gemm_args& g, int slices, hipStream_t s) {
-  pt_gemm_args p = g;
-  p.epi = EPI_STORE_F32;
-  p.K = g.K / slices; p.k_tracks = g.batch; p.batch = g.batch * slices;
-  p.out = g.sk_part; p.out_bstride = (int64_t)g.M * g.N; p.ldo = g.N;
-  return launch_epi<EPI_STORE_F32>(p, s, 2);
+  return launch_epi<EPI_STORE_F32>(pt_gemm_slices(g, slices), s, 2);
 }
 
 // The tile kernels with an LDS-staged QKV epilogue assume 32-row blocks inside one sequence at positions from a multiple

@@ -742,9 +742,7 @@ static bool skinny_covers(const pt_gemm_args& g) {
   return (int64_t)tiles * g.batch * 16 <= 0x7fffffff;
 }
 
-// Number of K slices the decode kernel would use for this residual GEMM when the caller is ready to add the
-// slices itself (0: the kernel does not cover the shape; 1: no split).
-// one to four rows: matrix-vector kernel, if A fits its LDS budget and the grid is at least half a round
+// One to four rows: matrix-vector kernel, if A fits its LDS budget and the grid is at least half a round.
 static bool use_gemv(const pt_gemm_args& g) {
   return g.M <= 4 && g.n_groups == 0 && pt_tune_skinny_plan == 0 && g.K % 512 == 0 &&
          (int64_t)(g.M == 3 ? 4 : g.M) * g.K * 2 <= 48 * 1024 && (int64_t)(g.N / 32) * g.batch >= 128;
@@ -754,21 +752,18 @@ bool pt_gemm_fuses_norm(const pt_gemm_args& g) {
   return skinny_covers(g) && use_gemv(g) && (g.epi == EPI_QKV || g.epi == EPI_SWIGLU) && g.lda == g.K;
 }
 
+// Number of K slices this kernel would use for a residual GEMM when the caller is ready to add the slices itself
+// (0: the kernel does not cover the shape; 1: no split).
 int pt_gemm_skinny_ksplit(const pt_gemm_args& g) {
-  if (g.M > 64 && g.n_groups == 0) return pt_gemm_mfma_ksplit(g);
   if (!skinny_covers(g)) return 0;
   if (g.epi != EPI_RESIDUAL || !g.sk_part || (g.N & 3) || use_gemv(g)) return 1;
   return plan_skinny(g, g.N / 32, 16).ks;
 }
 
-// Returns the kernel family launched (2, or 3 for the matrix-vector form), 0 if the shape is not covered.  With allow_split the K slices chosen by
-// pt_gemm_skinny_ksplit are left in g.sk_part instead of the finished residual stream.
+// Returns the kernel family launched (2, or 3 for the matrix-vector form), 0 if the shape is not covered.  With
+// allow_split the K slices chosen by pt_gemm_skinny_ksplit are left in g.sk_part instead of the finished residual stream.
 int pt_launch_gemm_skinny(const pt_gemm_args& g_in, bool allow_split, hipStream_t s) {
   pt_gemm_args g = g_in;
-  if (g.M > 64 && g.n_groups == 0) {
-    const int slices = allow_split ? pt_gemm_mfma_ksplit(g) : 1;
-    return slices > 1 ? pt_launch_gemm_mfma_split(g, slices, s) : 0;
-  }
   if (g.n_groups > 0) {
     // grouped: one batch entry per (track, group), each with at most grp_max_rows rows
     if (g.grp_max_rows > 64 || !g.grp_count || !g.grp_base || (g.w_gstride & 7)) return 0;

@@ -437,8 +437,8 @@ static int run_gemm(pt_handle* h, const pt_gemm_args& g_in, int cls) {
 }
 
 // Residual GEMM (out = res + A W^T) followed, when gain is given, by the RMSNorm of the new residual stream
-// into `normed`.  With few rows the GEMM may split K over workgroups; the kernel that adds the slices also adds the
-// residual and normalises.
+// into `normed`.  Where its tiles would leave compute units idle the GEMM may split K over workgroups (weight-streaming
+// kernel up to 64 rows, MFMA tile kernels above); the kernel that adds the slices also adds the residual and normalises.
 //
 // Otherwise, with more than 64 rows (MFMA tile kernels on both sides), the norm is folded into the two GEMMs instead.
 // The residual GEMM's epilogue also stores bf16(h * gain) into `normed` and per-row partial sums of squares;
@@ -454,7 +454,8 @@ static int run_residual_gemm_norm(pt_handle* h, const pt_gemm_args& g_in, int cl
   const int64_t rows = g.M;
   int rc;
   *folded_parts = 0;
-  const int slices = h->path == PT_PATH_AUTO && g.N == g.ldo && g.N <= 8192 ? pt_gemm_skinny_ksplit(g) : 1;
+  const int slices = h->path == PT_PATH_AUTO && g.N == g.ldo && g.N <= 8192
+                         ? (g.M > 64 ? pt_gemm_mfma_ksplit(g) : pt_gemm_skinny_ksplit(g)) : 1;
   if (slices <= 1 && h->path == PT_PATH_AUTO && g_fold_rmsnorm && gain && next && g.M > 64 && g.N == g.ldo && pt_gemm_mfma_covers(*next)) {
     const int parts = pt_gemm_mfma_fold_parts(g);
     if (parts > 0 && parts <= (g.N + 63) / 64) {
@@ -473,12 +474,13 @@ static int run_residual_gemm_norm(pt_handle* h, const pt_gemm_args& g_in, int cl
   if (slices > 1) {
     {
       prof_scope ps(h, cls);
-      rc = pt_launch_gemm_skinny(g, true, h->stream);
+      rc = g.M > 64 ? pt_launch_gemm_mfma_split(g, slices, h->stream) : pt_launch_gemm_skinny(g, true, h->stream);
       if (rc < 0) return rc;
-      if (rc == 0) return pt_set_error(PT_ERR_HIP, "decode GEMM refused a shape it had accepted");
+      if (rc == 0) return pt_set_error(PT_ERR_HIP, "a GEMM refused a shape that it had accepted with K slices");
       count_family(h, cls, rc);
     }
     prof_scope ps(h, PT_K_RMSNORM);
+    count_family(h, PT_K_RMSNORM, 1);
     return pt_launch_resnorm(g.sk_part, slices, g.res, g.res_bstride, g.out, g.out_bstride, gain, gain_bstride,
                              gain ? normed : nullptr, rows * g.N, g.batch, rows, g.N, c.rms_eps, h->stream);
   }

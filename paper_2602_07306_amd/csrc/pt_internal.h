@@ -73,7 +73,7 @@ struct pt_workspace {
   size_t off_o;       // dtype [T, rows, hq] attention output
   size_t off_m;       // dtype [T, rows, f]  SwiGLU product
   size_t off_part;    // fp32 split-K decode-attention partials, [T*B*H][max_splits][hd + 2]
-  size_t off_skp;     // fp32 K slices of the decode residual GEMMs, [slice][T][rows][d]
+  size_t off_skp;     // fp32 K slices of the residual GEMMs, [slice][T][rows][d]
   size_t off_ss;      // fp32 [T, rows, d / 64] per-row partial sums of squares (RMSNorm folded into the GEMMs)
   size_t off_rinv;    // fp32 [T, rows] 1/rms of every row, from those sums
   size_t off_rowmap;  // int2 [rows] (sequence, position) of every row of a ragged batch
@@ -187,7 +187,7 @@ struct pt_gemm_args {
   // (the padded-packed layout of a ragged prefill), which the LDS-staged QKV epilogue relies on.
   const int2* row_map;
   int32_t row_blocks;
-  // K-slice scratch of the decode kernel, sk_part_floats floats (may be null: K is not split over workgroups)
+  // K-slice scratch of residual GEMMs, sk_part_floats floats (may be null: K is not split over workgroups)
   float* sk_part;
   int64_t sk_part_floats;
   // Optional, honoured only where pt_gemm_fuses_norm(g) holds: A is not read; row m of track b is
@@ -230,8 +230,8 @@ struct pt_gemm_args {
 };
 
 enum { PT_SK_PART_FLOATS = 16 << 20 };   // K-slice scratch inside the caller's workspace arena
-enum { PT_MAX_SPLITS = 32 };
-enum { PT_STATIC_SCRATCH_BYTES = 32 << 20 };   // the static device array behind pt_decode_step_static             // decode-attention splits per (track, sequence, head)
+enum { PT_MAX_SPLITS = 32 };                   // decode-attention splits per (track, sequence, head)
+enum { PT_STATIC_SCRATCH_BYTES = 32 << 20 };   // the static device array behind pt_decode_step_static
 
 int pt_launch_gemm_generic(const pt_gemm_args& g, hipStream_t s);
 // Tuned launchers return 0 if they do not cover the problem (nothing launched), a negative PT_ERR_* code,
@@ -244,12 +244,20 @@ int pt_gemm_mfma_fold_parts(const pt_gemm_args& g);
 // K slices with which the MFMA tile kernels would run this residual GEMM when the caller adds the slices (1: no split);
 // pt_launch_gemm_mfma_split leaves them in g.sk_part, [slice][batch][M][N] fp32, as the weight-streaming kernel does.
 int pt_gemm_mfma_ksplit(const pt_gemm_args& g);
-int pt_launch_gemm_mfma_split(const pt_gemm_args& g, int slices, hipStream_t s);
+int pt_launch_gemm_mfma_split(const pt_gemm_args& g, int slices, hipStream_t s);   // returns 1
+// The launch that leaves them there: every slice of every track is a batch entry of its own.
+static inline pt_gemm_args pt_gemm_slices(const pt_gemm_args& g, int slices) {
+  pt_gemm_args p = g;
+  p.epi = EPI_STORE_F32;
+  p.K = g.K / slices; p.k_tracks = g.batch; p.batch = g.batch * slices;
+  p.out = g.sk_part; p.out_bstride = (int64_t)g.M * g.N; p.ldo = g.N;
+  return p;
+}
 // True if the MFMA tile kernels cover the problem (shape fields only).
 bool pt_gemm_mfma_covers(const pt_gemm_args& g);
 // Weight-streaming kernel for M <= 64 (decode): returns 2, or 3 for its matrix-vector form (M <= 4).  With
-// allow_split a residual GEMM (of more rows as well: the MFMA tile kernels then, returning 1) may leave pt_gemm_skinny_ksplit(g) > 1 K slices in g.sk_part
-// ([slice][batch][M][N] fp32) instead of writing out = res + product; pt_launch_resnorm adds them up.
+// allow_split a residual GEMM may leave pt_gemm_skinny_ksplit(g) > 1 K slices in g.sk_part ([slice][batch][M][N] fp32)
+// instead of writing out = res + product; pt_launch_resnorm adds them up.
 int pt_launch_gemm_skinny(const pt_gemm_args& g, bool allow_split, hipStream_t s);
 int pt_gemm_skinny_ksplit(const pt_gemm_args& g);
 // True if pt_launch_gemm_skinny would run this problem (shape fields only) on the kernel that can form its A

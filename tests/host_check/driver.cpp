@@ -249,6 +249,8 @@ int main() {
   };
   for (int mode = 0; mode < 2; ++mode)
     for (const pt_config& c : models) run_model(c, mode);
-  printf("host_check: %ld launches, %ld buffers checked, all inside their memory\n", hc_launches(), hc_checked());
+  EXPECT(hc_sliced() > 0);
+  printf("host_check: %ld launches (%ld sliced GEMMs above 64 rows), %ld buffers checked, all inside their memory\n",
+         hc_launches(), hc_sliced(), hc_checked());
   return 0;
 }

@@ -10,6 +10,7 @@ void hc_clear_ranges(void);
 void hc_set_mode(int mode);     // 0: tuned kernels refuse every shape, 1: they accept what the real ones would
 long hc_checked(void);          // buffers checked so far
 long hc_launches(void);         // launches seen so far
+long hc_sliced(void);           // of these, residual GEMMs of more than 64 rows that left K slices
 void* hc_scratch_address(void); // the address hipGetSymbolAddress reports for the static scratch array (driver's)
 #ifdef __cplusplus
 }

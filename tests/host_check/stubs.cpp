@@ -16,7 +16,7 @@
 namespace {
 struct range { uintptr_t lo, hi; const char* name; };
 std::vector<range> g_ranges;
-long g_checked = 0, g_launches = 0;
+long g_checked = 0, g_launches = 0, g_sliced = 0;
 int g_mode = 0;
 
 void need(const void* p, double bytes, const char* what) {
@@ -38,6 +38,8 @@ void check_gemm(const pt_gemm_args& g, const char* who) {
   const int es = esize(g.dtype);
   const int groups = g.blk_group ? (g.n_groups > 0 ? g.n_groups : 1) : 1;
   for (int b = 0; b < g.batch; ++b) {
+    const int bt = g.k_tracks > 0 ? b % g.k_tracks : b;                       // track and first element of a K slice
+    const size_t k0 = g.k_tracks > 0 ? (size_t)(b / g.k_tracks) * g.K : 0;
     if (g.norm_src) {
       need(g.norm_src + b * g.norm_bstride, ((double)(g.M - 1) * g.K + g.K) * 4, "GEMM norm_src");
       need(g.norm_gain + b * g.norm_gbstride, g.K * 4.0, "GEMM norm_gain");
@@ -47,10 +49,10 @@ void check_gemm(const pt_gemm_args& g, const char* who) {
       if (g.a_bstride <= 0 || g.a_bstride % g.lda) { fprintf(stderr, "host_check: %s gathers rows but a_bstride is not a whole number of rows\n", who); abort(); }
       need((const char*)g.A + (size_t)b * g.a_bstride * es, (double)g.a_bstride * es, "GEMM A (gathered)");
     } else {
-      need((const char*)g.A + (size_t)b * g.a_bstride * es, ((double)(g.M - 1) * g.lda + g.K) * es, "GEMM A");
+      need((const char*)g.A + ((size_t)bt * g.a_bstride + k0) * es, ((double)(g.M - 1) * g.lda + g.K) * es, "GEMM A");
     }
     for (int e = 0; e < groups; ++e)
-      need((const char*)g.W + ((size_t)b * g.w_bstride + (size_t)e * g.w_gstride) * es, ((double)(g.N - 1) * g.ldb + g.K) * es, "GEMM W");
+      need((const char*)g.W + ((size_t)bt * g.w_bstride + (size_t)e * g.w_gstride + k0) * es, ((double)(g.N - 1) * g.ldb + g.K) * es, "GEMM W");
     if (g.blk_group) need(g.blk_group + b * g.grp_bstride, (g.M / 64) * 4.0, "GEMM blk_group");
     if (g.grp_count) {
       need(g.grp_count + b * g.grp_info_bstride, g.n_groups * 4.0, "GEMM grp_count");
@@ -109,10 +111,11 @@ extern "C" void hc_clear_ranges(void) { g_ranges.clear(); }
 extern "C" void hc_set_mode(int mode) { g_mode = mode; }
 extern "C" long hc_checked(void) { return g_checked; }
 extern "C" long hc_launches(void) { return g_launches; }
+extern "C" long hc_sliced(void) { return g_sliced; }
 
 // ------------------------------------------------------------------------------------------------ GEMM family
 // mode 0: the tuned kernels refuse everything (generic path); mode 1: they take everything they are offered,
-// fold the norm where asked and split K in the decode residual GEMMs.
+// fold the norm where asked and split K in residual GEMMs of up to 256 rows.
 int pt_tune_gemm_cfg = -1, pt_tune_skinny_plan = 0, pt_tune_attn_prefill = 0;
 int pt_launch_gemm_generic(const pt_gemm_args& g, hipStream_t) { check_gemm(g, "generic GEMM"); return PT_OK; }
 bool pt_gemm_mfma_covers(const pt_gemm_args& g) { return g_mode == 1 && g.dtype == PT_BF16 && g.K % 128 == 0; }
@@ -123,6 +126,18 @@ int pt_launch_gemm_mfma(const pt_gemm_args& g, hipStream_t) {
 }
 int pt_gemm_mfma_fold_parts(const pt_gemm_args& g) {
   return pt_gemm_mfma_covers(g) && g.epi == EPI_RESIDUAL && g.N % 128 == 0 ? g.N / 128 : 0;
+}
+int pt_gemm_mfma_ksplit(const pt_gemm_args& g) {
+  if (!pt_gemm_mfma_covers(g) || g.epi != EPI_RESIDUAL || g.M > 256 || g.blk_group || !g.sk_part) return 1;
+  int ks = 16;
+  while (ks > 1 && ((int64_t)ks * g.batch * g.M * g.N > g.sk_part_floats || g.K % (ks * 128))) ks /= 2;
+  return ks;
+}
+int pt_launch_gemm_mfma_split(const pt_gemm_args& g, int slices, hipStream_t) {
+  if ((int64_t)slices * g.batch * g.M * g.N > g.sk_part_floats) { fprintf(stderr, "host_check: K slices exceed their scratch\n"); abort(); }
+  check_gemm(pt_gemm_slices(g, slices), "MFMA GEMM, K slices");
+  ++g_sliced;
+  return 1;
 }
 static bool skinny_ok(const pt_gemm_args& g) { return g_mode == 1 && g.dtype == PT_BF16 && g.K % 512 == 0 && g.N % 32 == 0; }
 int pt_gemm_skinny_ksplit(const pt_gemm_args& g) {
