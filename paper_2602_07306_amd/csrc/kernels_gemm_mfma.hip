@@ -60,6 +60,28 @@ static double tile_us(const pt_gemm_args& g, int cfg, int slices) {
   return 9.5 + rounds * 0.585 * steps;
 }
 
+// Grouped GEMM.  Above 32 rows in an average group: the largest tile, also where a group fills a small part of it.  Group
+// sizes scatter, each tile past a group's first re-reads its weights, and the reads of the weights are the time: 4 tracks
+// x 8 experts of width 2048 on K = 1024, gate/up and down in us with 256 rows: 106 + 58 (256 x 256) against 109 + 73
+// (128 x 256), 175 + 82 (64 x 256) and 158 + 77 (32 x 256); 512 rows: 106 + 58 against 126 + 73 (128 x 256).
+// With fewer rows a tile is nearly empty and its fixed cost counts.  gate/up: 256 x 256 still wins where a group's weights
+// take long to read (same experts, 96 rows: 90 against 106 and 170; 8 tracks x 64 experts of width 256 on K = 2048: 277
+// against 302 and 362), 32 x 256 where they are small and tiles fill the chip at least once (4 tracks on K = 1024, 96
+// rows: 64 experts of width 256 111 against 120 us, 32 of width 512 108 against 115, 16 of 512 66 against 71; not with
+// 64 of width 512, 198 against 189).  down: 32 x 256 under the same condition (64 experts of width 256: 90 against 113;
+// 32 of 256: 53 against 64), else 128 x 256 (8 experts of width 2048: 48 against 57; 16 of 1024: 54 against 75; 8 tracks
+// x 32 of 1024 on width 2048: 386 against 438).
+static int choose_grouped(const pt_gemm_args& g) {
+  if (g.grp_rows > 0 && g.grp_rows <= 32) {
+    const int64_t weights = (int64_t)g.N * g.K;   // elements of a group's matrix
+    const int64_t tiles = (int64_t)g.n_groups * g.batch * ((g.N + 255) / 256);
+    const bool small = weights <= 512 * 1024 || (g.epi == EPI_SWIGLU && weights <= 1024 * 1024 && tiles <= 512 && g.grp_rows <= 24);
+    if (g.K <= 1024 && small && tiles >= 256 && cfg_fits(g, 5)) return 5;
+    if (g.epi == EPI_STORE_F32) return 4;
+  }
+  return cfg_fits(g, 0) ? 0 : -1;
+}
+
 // The tile configuration for a problem, or -1 if the family does not cover it (-2: nothing to do).
 static int choose_cfg(const pt_gemm_args& g) {
   if (g.dtype != PT_BF16) return -1;
@@ -74,12 +96,7 @@ static int choose_cfg(const pt_gemm_args& g) {
   if (g.epi == EPI_SWIGLU && ((g.olp_bstride & 7) || ((uintptr_t)g.olp & 15))) return -1;
   if (pt_tune_gemm_cfg >= 0 && pt_tune_gemm_cfg < GM_NCFG) return cfg_fits(g, pt_tune_gemm_cfg) ? pt_tune_gemm_cfg : -1;
   static const int m64[] = {3, 6, -1}, m32[] = {5, 7, -1}, odd[] = {8, 10, -1};
-  // Grouped GEMM: the largest tile, also where an average group fills a small part of it.  Group sizes scatter, each
-  // tile past a group's first re-reads its weights, and the reads of the weights are the time: 4 tracks x 8 experts of
-  // width 2048 on K = 1024, gate/up and down in us with 96 rows: 89 + 57 (256 x 256) against 104 + 48 (128 x 256),
-  // 160 + 62 (64 x 256) and 170 + 71 (32 x 256); 256 rows: 107 + 58, 107 + 72, 176 + 82, 148 + 77; 512 rows: 104 + 60
-  // against 123 + 72 (128 x 256).
-  if (g.blk_group && cfg_fits(g, 0)) return 0;
+  if (g.blk_group) return choose_grouped(g);
   if (g.M <= 64) {
     for (const int* c = g.M <= 32 ? m32 : m64; *c >= 0; ++c)
       if (cfg_fits(g, *c)) return *c;

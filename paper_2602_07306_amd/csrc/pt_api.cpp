@@ -719,6 +719,7 @@ static int forward(pt_handle* h, const pt_workspace& w, const int32_t* dev_token
       g.A = abuf; g.a_bstride = rows * d; g.lda = (int32_t)d;
       g.a_rows = ma.perm; g.a_rows_bstride = ma.slots;
       g.blk_group = ma.blk; g.grp_bstride = ma.slots / 64; g.w_gstride = l.expert_elems;
+      g.grp_rows = (int32_t)((rows * c.top_k + c.n_experts - 1) / c.n_experts);
       g.grp_count = ma.cnt + moe_nblk * 64; g.grp_base = ma.cnt + (moe_nblk + 1) * 64; g.grp_info_bstride = (moe_nblk + 2) * 64;
       g.n_groups = c.n_experts; g.grp_max_rows = (int32_t)std::min<int64_t>(rows, 0x7fffffff);
       g.W = wexp; g.w_bstride = w_bstride; g.ldb = (int32_t)d;
@@ -731,6 +732,7 @@ static int forward(pt_handle* h, const pt_workspace& w, const int32_t* dev_token
       memset(&g, 0, sizeof(g));
       g.A = mbuf; g.a_bstride = ma.slots * f; g.lda = (int32_t)f;
       g.blk_group = ma.blk; g.grp_bstride = ma.slots / 64; g.w_gstride = l.expert_elems;
+      g.grp_rows = (int32_t)((rows * c.top_k + c.n_experts - 1) / c.n_experts);
       g.grp_count = ma.cnt + moe_nblk * 64; g.grp_base = ma.cnt + (moe_nblk + 1) * 64; g.grp_info_bstride = (moe_nblk + 2) * 64;
       g.n_groups = c.n_experts; g.grp_max_rows = (int32_t)std::min<int64_t>(rows, 0x7fffffff);
       g.W = wexp + (size_t)(l.wgu_elems * es); g.w_bstride = w_bstride; g.ldb = (int32_t)f;

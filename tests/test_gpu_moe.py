@@ -107,6 +107,11 @@ CASES = {
     # far more experts than a decode step has assignments: most expert segments are empty
     "sixteen_experts_mostly_empty": (dict(n_experts=16, top_k=2, n_layers=2, block_depth=2, d_model=512, n_heads=8,
                                           n_kv_heads=2, d_ffn=256), 1, 32, 3),
+    # prefills with few rows per expert: the small tile for small experts that fill the chip, the middle one for the down
+    # projection of few experts
+    "sixty_four_small_experts": (dict(n_tracks=4, n_experts=64, top_k=2, n_layers=2, block_depth=1, d_ffn=128, max_batch=1), 1, 97, 1),
+    "sixty_four_experts_more_rows_than_a_small_tile": (dict(n_tracks=4, n_experts=64, top_k=8, n_layers=2, block_depth=2, d_ffn=128), 2, 125, 1),
+    "eight_experts_few_rows": (dict(n_experts=8, top_k=1, n_layers=2, block_depth=1, d_ffn=256, max_batch=1), 1, 130, 1),
     # several 256-row counting blocks and GEMM tiles per expert, ragged last block
     "many_rows": (dict(n_experts=4, top_k=2, n_layers=2, block_depth=2, max_batch=3, max_seq=320), 3, 300, 1),
 }
