@@ -43,18 +43,19 @@ static bool cfg_fits(const pt_gemm_args& g, int cfg) {
 }
 
 // Expected time in us of a GEMM on tile configuration 0 (256 x 256), 4 (128 x 256) or 2 (128 x 128) with its K cut into
-// `slices`.  A launch runs in rounds of one tile per compute unit (two for configuration 2, whose LDS leaves room for
-// a second workgroup: its fills and epilogues hide behind the other's K loop, so they count once).  What bounds a round
-// is the latency of the K loop's loads, hence a fixed part and a part per K step of 64, fitted on one-round launches at
-// K = 1024 and 4096 (4 tracks, 16 to 64 workgroups): 33.8 / 82, 24.4 / 59.6 and 17.9 / 44.3 us.  It orders the
-// three correctly at M = 96 to 4096 of the Mid, Large and one-GPU-share shapes: e.g. 4 tracks x 1024 x 1024 rows,
+// `slices`.  A launch runs in rounds of one tile per compute unit.  The fixed part of configuration 2 counts once: its LDS
+// leaves room for a second workgroup, so the fills and epilogues of later rounds hide behind the other's K loop.  What
+// bounds a round is the latency of the K loop's loads, hence a fixed part and a part per K step of 64, fitted on
+// one-round launches at K = 1024 and 4096 (4 tracks, 16 to 64 workgroups): 33.8 / 82, 24.4 / 59.6 and 17.9 / 44.3 us.
+// It orders the three correctly at M = 96 to 4096 of the Mid, Large and one-GPU-share shapes: e.g. 4 tracks x 1024 x 1024 rows,
 // K = 4096: 88 / 65 / 49 us; 8 tracks x 256 x 2048, K = 8192: 172 / 120 / 91; 4 tracks x 1024 x 3072, K = 1024:
 // 40 / 48 / 41; 4 tracks x 4096 x 8192, K = 1024: 271 / 328 / 304.
 static double tile_us(const pt_gemm_args& g, int cfg, int slices) {
   const int bm = cfg == 0 ? 256 : 128, bn = cfg == 2 ? 128 : 256;
   const int64_t tiles = (int64_t)((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn) * g.batch * slices;
   const double steps = (double)g.K / (slices * GM_BK);
-  const double rounds = (double)((tiles + 255) / 256);
+  const int64_t n_cu = pt_device_cus();
+  const double rounds = (double)((tiles + n_cu - 1) / n_cu);
   if (cfg == 0) return rounds * (16.7 + 1.02 * steps);
   if (cfg == 4) return rounds * (12.4 + 0.735 * steps);
   return 9.5 + rounds * 0.585 * steps;
@@ -75,8 +76,8 @@ static int choose_grouped(const pt_gemm_args& g) {
   if (g.grp_rows > 0 && g.grp_rows <= 32) {
     const int64_t weights = (int64_t)g.N * g.K;   // elements of a group's matrix
     const int64_t tiles = (int64_t)g.n_groups * g.batch * ((g.N + 255) / 256);
-    const bool small = weights <= 512 * 1024 || (g.epi == EPI_SWIGLU && weights <= 1024 * 1024 && tiles <= 512 && g.grp_rows <= 24);
-    if (g.K <= 1024 && small && tiles >= 256 && cfg_fits(g, 5)) return 5;
+    const bool small = weights <= 512 * 1024 || (g.epi == EPI_SWIGLU && weights <= 1024 * 1024 && tiles <= 2 * pt_device_cus() && g.grp_rows <= 24);
+    if (g.K <= 1024 && small && tiles >= pt_device_cus() && cfg_fits(g, 5)) return 5;
     if (g.epi == EPI_STORE_F32) return 4;
   }
   return cfg_fits(g, 0) ? 0 : -1;
@@ -95,7 +96,7 @@ static int choose_cfg(const pt_gemm_args& g) {
       ((g.ldo & 3) || (g.N & 3) || (g.out_bstride & 3) || (g.res_bstride & 3) || (((uintptr_t)g.out | (uintptr_t)g.res) & 15))) return -1;
   if (g.epi == EPI_SWIGLU && ((g.olp_bstride & 7) || ((uintptr_t)g.olp & 15))) return -1;
   if (pt_tune_gemm_cfg >= 0 && pt_tune_gemm_cfg < GM_NCFG) return cfg_fits(g, pt_tune_gemm_cfg) ? pt_tune_gemm_cfg : -1;
-  static const int m64[] = {3, 6, -1}, m32[] = {5, 7, -1}, odd[] = {8, 10, -1};
+  static const int m64[] = {3, 6, -1}, m32[] = {5, 7, -1};
   if (g.blk_group) return choose_grouped(g);
   if (g.M <= 64) {
     for (const int* c = g.M <= 32 ? m32 : m64; *c >= 0; ++c)
@@ -108,8 +109,6 @@ static int choose_cfg(const pt_gemm_args& g) {
     const double us = cfg_fits(g, cfg) ? tile_us(g, cfg, 1) : 1e30;
     if (us < best_us) { best_us = us; best = cfg; }
   }
-  for (const int* c = odd; best < 0 && *c >= 0; ++c)   // head widths that only these own whole
-    if (cfg_fits(g, *c)) best = *c;
   return best;
 }
 

@@ -636,8 +636,6 @@ static int pt_tune_skinny_items = 0;   // 0: automatic; 1: one group of tiles pe
 
 struct sk_plan { int wpt, ks; };
 
-static int device_cus();
-
 template <int MI, int RBHI, int EPI>
 static int launch_skinny_rb(const pt_gemm_args& g, int tiles, sk_plan p, hipStream_t s) {
   constexpr int RING = 4 * (MI + RBHI) * 32 * 128, RED = 4 * MI * 16 * 64 * 4;
@@ -647,7 +645,7 @@ static int launch_skinny_rb(const pt_gemm_args& g, int tiles, sk_plan p, hipStre
   int items = 1;
   if (tiles % p.wpt == 0 && g.n_groups == 0 && pt_tune_skinny_items != 1) {
     const int64_t total = (int64_t)p.wpt * g.batch * p.ks;
-    const int64_t resident = (int64_t)device_cus() * ((160 * 1024) / LDS >= 3 ? 3 : (160 * 1024) / LDS >= 2 ? 2 : 1);
+    const int64_t resident = (int64_t)pt_device_cus() * ((160 * 1024) / LDS >= 3 ? 3 : (160 * 1024) / LDS >= 2 ? 2 : 1);
     for (int d = 2; d <= 16; ++d)
       if (p.wpt % d == 0 && total / d >= resident) items = d;
     if (pt_tune_skinny_items > 1 && p.wpt % pt_tune_skinny_items == 0) items = pt_tune_skinny_items;
@@ -661,15 +659,13 @@ static int launch_skinny_rb(const pt_gemm_args& g, int tiles, sk_plan p, hipStre
   return 2;
 }
 
-static int device_cus() {
-  static int n = 0;
-  if (!n) {
+int pt_device_cus() {
+  static const int n = [] {
     int dev = 0, v = 0;
     if (hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0)
-      n = v;
-    else
-      n = 256;
-  }
+      return v;
+    return 256;
+  }();
   return n;
 }
 
@@ -678,7 +674,7 @@ static int device_cus() {
 // cost of about six steps) and with the rows it loads per step (its tiles of W plus the shared A rows).
 // K slices (ks_max > 1: residual GEMMs whose caller adds the slices) shorten the rounds of shapes with few tiles.
 static sk_plan plan_skinny(const pt_gemm_args& g, int tiles, int ks_max) {
-  const int n_cu = device_cus();
+  const int n_cu = pt_device_cus();
   const double a_rows = g.M > 32 ? 0.6 : 0.3;
   sk_plan best = {(tiles + 3) / 4, 1};
   double best_cost = 1e30;

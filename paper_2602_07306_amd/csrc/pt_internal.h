@@ -234,6 +234,7 @@ enum { PT_SK_PART_FLOATS = 16 << 20 };   // K-slice scratch inside the caller's 
 enum { PT_MAX_SPLITS = 32 };                   // decode-attention splits per (track, sequence, head)
 enum { PT_STATIC_SCRATCH_BYTES = 32 << 20 };   // the static device array behind pt_decode_step_static
 
+int pt_device_cus();   // compute units of the current device
 int pt_launch_gemm_generic(const pt_gemm_args& g, hipStream_t s);
 // Tuned launchers return 0 if they do not cover the problem (nothing launched), a negative PT_ERR_* code,
 // or the kernel family that was launched (the numbering of pt_profile_paths).
