@@ -520,7 +520,9 @@ __global__ void __launch_bounds__(256) gemm_gemv_kernel(const pt_gemm_args g, in
         const float lo[4] = {lo4.x, lo4.y, lo4.z, lo4.w}, hi[4] = {hi4.x, hi4.y, hi4.z, hi4.w};
         sk_finish<EPI>(g, b, cur_unit / KW, lane, row_of(cur_unit), 0, 1, lo, hi);
       }
-      if constexpr (KW > 1) __syncthreads();   // the sums are read before the next unit's replace them
+      // the sums are read before the next unit's replace them (grids of launch_gemv with KW > 1 give every workgroup one
+      // unit, but the kernel takes any number)
+      if constexpr (KW > 1) __syncthreads();
       else __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 #pragma unroll
       for (int r = 0; r < 8; ++r)
