@@ -217,7 +217,6 @@ struct pt_gemm_args {
   int64_t a_rows_bstride;
   const int32_t* blk_group;
   int64_t grp_bstride, w_gstride;
-  int32_t grp_rows;   // rows an average group holds (for the choice of the tile; 0 = unknown)
   // The same groups as (first row, row count) per group, for the weight-streaming kernel, which takes a whole
   // group per workgroup when no group can hold more than 64 rows (grp_max_rows): group e of track b has
   // grp_count[b * grp_info_bstride + e] rows starting at row grp_base[b * grp_info_bstride + e].
@@ -225,6 +224,7 @@ struct pt_gemm_args {
   const int32_t* grp_base;
   int64_t grp_info_bstride;
   int32_t n_groups, grp_max_rows;
+  int32_t grp_rows;   // rows an average group holds (for the choice of the tile; 0 = unknown)
   // K slices (MFMA tile kernels, EPI_STORE_F32 only): when k_tracks > 0, batch entry b is slice b / k_tracks of track
   // b % k_tracks; K is the length of one slice and slice s starts at element s * K of every row of A and W.
   int32_t k_tracks;
