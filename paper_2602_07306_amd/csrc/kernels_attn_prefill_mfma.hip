@@ -49,12 +49,59 @@ union pk8 {
 // ------------------------------------------------------------------------------------------------
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
+// `rows` query rows from position q0 on, one after the other: lane = key for the scores, lane = head-dim index for the
+// values, no key after a row's own position touched.  q and o point at the first row, `pitch` elements from row to row.
+template <int HD>
+__device__ __forceinline__ void attn_rows_one_by_one(const bf16_t* q, bf16_t* o, int64_t pitch, const bf16_t* K, const bf16_t* Vt,
+                                                     int s_pad, int q0, int rows, int lane) {
+  const float c_log2 = 1.4426950408889634f / sqrtf((float)HD);
+  for (int r = 0; r < rows; ++r, q += pitch, o += pitch) {
+    const int nkeys = q0 + r + 1;
+    float m = -INFINITY, l = 0.f, acc[HD / 64];
+#pragma unroll
+    for (int i = 0; i < HD / 64; ++i) acc[i] = 0.f;
+    for (int base = 0; base < nkeys; base += 64) {
+      const int key = base + lane;
+      float s = -INFINITY;
+      if (key < nkeys) {
+        const uint32_t* kr = (const uint32_t*)(K + (int64_t)key * HD);
+        float dot = 0.f;
+#pragma unroll 4
+        for (int e = 0; e < HD / 2; ++e) {
+          const uint32_t qw = ((const uint32_t*)q)[e], kw = kr[e];
+          dot = fmaf(__uint_as_float(qw << 16), __uint_as_float(kw << 16), dot);
+          dot = fmaf(__uint_as_float(qw & 0xffff0000u), __uint_as_float(kw & 0xffff0000u), dot);
+        }
+        s = dot * c_log2;
+      }
+      const float m_new = fmaxf(m, wave_max(s));
+      const float corr = __builtin_amdgcn_exp2f(m - m_new);
+      const float p = key < nkeys ? __builtin_amdgcn_exp2f(s - m_new) : 0.f;
+      l = l * corr + wave_sum(p);
+      m = m_new;
+#pragma unroll
+      for (int i = 0; i < HD / 64; ++i) acc[i] *= corr;
+      const int nk = min(64, nkeys - base);
+      for (int kk = 0; kk < nk; ++kk) {
+        const float pk = __shfl(p, kk, 64);
+#pragma unroll
+        for (int i = 0; i < HD / 64; ++i) acc[i] = fmaf(pk, elem<bf16_t>::ld(Vt + (int64_t)(lane + 64 * i) * s_pad + base + kk), acc[i]);
+      }
+    }
+    const float inv = 1.0f / l;
+#pragma unroll
+    for (int i = 0; i < HD / 64; ++i) elem<bf16_t>::st(o + lane + 64 * i, acc[i] * inv);
+  }
+}
+
 // PF: operand fragments in flight between LDS and the matrix cores.
 // TAIL: the length need not be a multiple of 64 (a template argument: the other form has no masks in its loop).  The
 // last key tile then holds cache positions that no token has written: the causal mask drops their scores (for every row
 // that is stored), and their columns of V^T are zeroed on the way into LDS, because their bytes may be anything and
 // 0 * NaN is not 0.  Query rows past the end repeat the last one and are not stored.  The cache holds max_seq rounded
 // up to 64 positions, so the whole tile may be read.
+// These lengths also keep a value that is no number from rows before its own: a key that the mask drops still enters the
+// product, as 0 * V, so a wavefront whose result holds an infinity or a NaN computes its rows one by one instead.
 // PIECES: bf16 numbers that a probability is multiplied with V as.  One rounds it to 8 bits of significand; three hold
 // all 24 of fp32 (each is the rounded remainder of those before it, and the remainders are exact).
 template <int HD, int PF, bool TAIL, int PIECES>
@@ -293,8 +340,21 @@ __global__ void __launch_bounds__(256, HD == 64 ? 3 : 2) attn_prefill_lds_kernel
   }
   if (!active) return;
   const float l = l_run + __shfl_xor(l_run, 32, 64);
-  if (TAIL && q0 + l32 >= slen) return;
   const float inv = 1.0f / l;
+  if constexpr (TAIL) {
+    float z = inv * 0.f;   // NaN if any factor or sum of this lane is no number
+#pragma unroll
+    for (int hb = 0; hb < HB; ++hb)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) z = fmaf(oacc[hb][v], 0.f, z);
+    const bool mine = q0 + l32 < slen;
+    if (__any(mine && z != z)) {
+      const int64_t first = t * a.q_bstride + (row0 + q0) * (a.H * HD) + head * HD;
+      attn_rows_one_by_one<HD>((const bf16_t*)a.q + first, (bf16_t*)a.o + first, a.H * HD, K, Vt, a.s_pad, q0, min(32, slen - q0), lane);
+      return;
+    }
+    if (!mine) return;
+  }
   bf16_t* orow = (bf16_t*)a.o + qoff;
 #pragma unroll
   for (int hb = 0; hb < HB; ++hb)
