@@ -27,6 +27,12 @@ int pt_set_error(int code, const char* fmt, ...) {
   return code;
 }
 
+int pt_device_cus() {
+  int dev = 0, v = 0;
+  if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v <= 0) return 256;
+  return v;
+}
+
 #define TILE_CHECK(expr) do { if ((expr) != hipSuccess) return -6; } while (0)
 
 extern "C" int pt_gemm_tile_clocks(int32_t epilogue, const void* dev_a, const void* dev_w, void* dev_out, void* dev_out_bf16,

@@ -3,6 +3,8 @@
 //   C[t] (M x N) = A[t] (M x K) * W[t]^T,   W[t] stored [N, K], for every track t (grid z-like dim)
 //
 // Both operands are contiguous along K, so a lane's 8-element MFMA operand is one 16-byte LDS read.
+// The square tiles (256 x 256 and 128 x 128) run the persistent kernel of gemm_tile_impl.h; the rest of this file is the
+// register-staged kernel of the other tiles.
 // Tiling: a workgroup owns a BM x BN tile; WM x WN wavefronts each own a (BM/WM) x (BN/WN) sub-tile
 // made of 32x32x16 MFMAs.  K advances in steps of 64 through a double-buffered LDS tile whose
 // 16-byte chunks are XOR-swizzled by the row number, so that neither the 16-byte stores (8 lanes per
@@ -125,14 +127,15 @@ typedef float f32x4_t __attribute__((ext_vector_type(4)));
 // the K loop, 3 past the barrier, 4 end of the epilogue; 6 and 7 the constant 100 MHz counter at entry and exit.
 #ifdef PT_GEMM_STAMPS
 __device__ long long* pt_gemm_stamps = nullptr;
-#define PT_STAMP(i)                                                                                                    \
+#define PT_STAMP_TILE(tile, i)                                                                                         \
   do {                                                                                                                 \
     if ((threadIdx.x & 63) == 0 && pt_gemm_stamps)                                                                     \
-      pt_gemm_stamps[((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * 8 + (i)] = ((i) >= 6) ? wall_clock64() : clock64(); \
+      pt_gemm_stamps[((int64_t)(tile) * 4 + (threadIdx.x >> 6)) * 8 + (i)] = ((i) >= 6) ? wall_clock64() : clock64(); \
   } while (0)
 #else
-#define PT_STAMP(i) ((void)0)
+#define PT_STAMP_TILE(tile, i) ((void)0)
 #endif
+#define PT_STAMP(i) PT_STAMP_TILE(blockIdx.x, i)
 
 // Element v of an accumulator tile.  Kernels whose accumulators fill the accumulation registers (more than 128 per
 // lane) read them with an explicit v_accvgpr_read at the point of use: left to itself, the register allocator moves
@@ -682,9 +685,21 @@ __device__ __forceinline__ void gemm_epilogue(const pt_gemm_args& g, f32x16_t (&
   }
 }
 
+#include "gemm_tile_impl.h"
+
+// The tiles that square_tile_run covers.
+template <int BM, int BN, int WM, int WN, int BK>
+constexpr bool is_square_tile = BM == BN && (BM == 256 || BM == 128) && WM == 2 && WN == 2 && BK == 64;
+
 template <int BM, int BN, int WM, int WN, int BK, int EPI>
 __global__ void __launch_bounds__(WM * WN * 64, (2 * (BM + BN) * BK * 2 <= 80 * 1024 && BM * BN <= 256 * 128 && WM * WN == 4) ? 2 : 1)
 gemm_mfma_kernel(const pt_gemm_args g, int tiles_m, int tiles_n) {
+  if constexpr (is_square_tile<BM, BN, WM, WN, BK>) {
+#if defined(__HIP_DEVICE_COMPILE__)   // the buffer types exist on the device only
+    square_tile_run<BM, 2, EPI>(tiles_m, tiles_n);
+#endif
+    return;
+  } else {
   PT_STAMP(6);
   PT_STAMP(0);
   constexpr int NT = WM * WN * 64;
@@ -790,14 +805,10 @@ gemm_mfma_kernel(const pt_gemm_args g, int tiles_m, int tiles_n) {
   for (int i = 0; i < A_CH; ++i) *(u32x4_t*)(As + st_dst + i * ST_STRIDE) = a_reg[0][i];
 #pragma unroll
   for (int i = 0; i < B_CH; ++i) *(u32x4_t*)(Bs + st_dst + i * ST_STRIDE) = w_reg[0][i];
-  // The largest tile leaves the loads of K step 2 to its first iteration, between the MFMAs.
-  constexpr bool LATE2 = BM * BN >= 256 * 256;
-  if constexpr (!LATE2) {
 #pragma unroll
-    for (int i = 0; i < A_CH; ++i) load_a(0, i, min(2, KT - 1));
+  for (int i = 0; i < A_CH; ++i) load_a(0, i, min(2, KT - 1));
 #pragma unroll
-    for (int i = 0; i < B_CH; ++i) load_w(0, i, min(2, KT - 1));
-  }
+  for (int i = 0; i < B_CH; ++i) load_w(0, i, min(2, KT - 1));
   __syncthreads();
   bf16x8_t af[2][MI], bfr[2][NI];
 #pragma unroll
@@ -813,13 +824,9 @@ gemm_mfma_kernel(const pt_gemm_args g, int tiles_m, int tiles_n) {
 
   f32x16_t acc[MI][NI];
 
-  // FIRST: the iteration of K step 0, which also loads K step 2 into the staging set that the pipeline fill has
-  // just parked (a wavefront can keep 63 loads in flight: issued in front of the loop, those loads would hold
-  // the first MFMA back until the loads of K step 1 have returned).
-  auto iteration = [&](auto PAR, auto FIRST_, int kt) {
+  auto iteration = [&](auto PAR, int kt) {
     constexpr int cur = decltype(PAR)::value;          // LDS buffer being multiplied
-    constexpr bool FIRST = decltype(FIRST_)::value;
-    constexpr int PER = FIRST ? 3 : 2;                  // memory instructions per staging chunk
+    constexpr int PER = 2;                              // memory instructions per staging chunk
     constexpr int wset = cur ^ 1;                       // staging set stored, then reloaded
     const bf16_t* Ac = As + cur * BM * BK;
     const bf16_t* Bc = Bs + cur * BN * BK;
@@ -846,12 +853,8 @@ gemm_mfma_kernel(const pt_gemm_args g, int tiles_m, int tiles_n) {
             bfr[fb][r - MI] = *(const bf16x8_t*)(src + (r - MI) * 32 * BK);
           } else {
             constexpr int e = kk * EXS + (r - FR) / PER;   // staging chunk: parked, then refilled right away
-            constexpr int what = (r - FR) % PER + (FIRST ? 0 : 1);   // 0: load of K step 2, 1: park, 2: refill
             if constexpr (e < EX && kk < NS) {
-              if constexpr (what == 0) {
-                if constexpr (e < A_CH) load_a(cur, e, min(2, KT - 1));
-                else load_w(cur, e - A_CH, min(2, KT - 1));
-              } else if constexpr (what == 1) {
+              if constexpr ((r - FR) % PER == 0) {
                 if constexpr (e < A_CH) *(u32x4_t*)(An + st_dst + e * ST_STRIDE) = a_reg[wset][e];
                 else *(u32x4_t*)(Bn + st_dst + (e - A_CH) * ST_STRIDE) = w_reg[wset][e - A_CH];
               } else {
@@ -873,13 +876,9 @@ gemm_mfma_kernel(const pt_gemm_args g, int tiles_m, int tiles_n) {
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[mi][ni][v] = 0.f;
   PT_STAMP(1);
-  if constexpr (LATE2) {
-    iteration(std::integral_constant<int, 0>{}, std::true_type{}, 0);
-    iteration(std::integral_constant<int, 1>{}, std::false_type{}, 1);
-  }
-  for (int kt = LATE2 ? 2 : 0; kt < KT; kt += 2) {
-    iteration(std::integral_constant<int, 0>{}, std::false_type{}, kt);
-    iteration(std::integral_constant<int, 1>{}, std::false_type{}, kt + 1);
+  for (int kt = 0; kt < KT; kt += 2) {
+    iteration(std::integral_constant<int, 0>{}, kt);
+    iteration(std::integral_constant<int, 1>{}, kt + 1);
   }
   PT_STAMP(2);
   if (has_rs && tid < BM) rs_inv[tid] = rs_mine;
@@ -898,6 +897,7 @@ gemm_mfma_kernel(const pt_gemm_args g, int tiles_m, int tiles_n) {
   gemm_epilogue<MI, NI, EPI, STAGED, STAGE_ELEMS>(g, acc, stage, b, wave_m, wave_n, lane, has_rs ? rs_inv + wm * TM : nullptr);
   PT_STAMP(4);
   PT_STAMP(7);
+  }
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1067,12 +1067,32 @@ static int launch_dl(const pt_gemm_args& g, hipStream_t s) {
 template <int BM, int BN, int WM, int WN, int BK, int EPI>
 static int launch_cfg(const pt_gemm_args& g, hipStream_t s) {
   const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
-  const size_t lds = (size_t)2 * (BM + BN) * BK * sizeof(bf16_t);
+  constexpr bool SQUARE = is_square_tile<BM, BN, WM, WN, BK>;
+  const size_t lds = SQUARE ? square_tile<BM, 2>::LDS : (size_t)2 * (BM + BN) * BK * sizeof(bf16_t);
   auto kern = gemm_mfma_kernel<BM, BN, WM, WN, BK, EPI>;
   PT_SET_MAX_LDS_ONCE(kern, lds);
   const int64_t total = (int64_t)tiles_m * tiles_n * g.batch;
   if (total > 0x7fffffff) return pt_set_error(PT_ERR_INVALID_ARGUMENT, "GEMM grid too large");
-  const unsigned grid = (unsigned)total;
+  unsigned grid = (unsigned)total;
+  if constexpr (SQUARE && BM == 128) {
+    // Four K steps of loads in flight, one workgroup per compute unit, instead of two with two steps each: where tiles
+    // leave no second workgroup (us, two steps / four: 4 tracks x 300 rows x 1024, K = 4096 33.7 / 29.1; 8 x 256 x 2048,
+    // K = 8192 112 / 97), and where one tile covers the rows, so that the weights' way from HBM is the time and K is not
+    // long enough to hide the tiles' ends (8 tracks x 96 rows x 16384: K = 2048 129 / 124, but K = 8192 176 / 195).
+    if ((total <= pt_device_cus() || (tiles_m == 1 && g.K < 4096)) && g.K >= 4 * BK) {
+      auto deep = gemm_tile_deep_kernel<BM, 4, EPI>;
+      PT_SET_MAX_LDS_ONCE(deep, (square_tile<BM, 4>::LDS));
+      const unsigned resident = (unsigned)pt_device_cus();
+      if (grid > resident) grid = resident >= 8 ? resident & ~7u : resident;
+      hipLaunchKernelGGL(deep, dim3(grid), dim3(WM * WN * 64), (square_tile<BM, 4>::LDS), s, g, tiles_m, tiles_n);
+      PT_HIP_CHECK(hipGetLastError());
+      return 1;
+    }
+  }
+  if constexpr (SQUARE) {   // as many workgroups as are resident; a multiple of 8 keeps a workgroup's tiles on its XCD
+    const unsigned resident = (unsigned)pt_device_cus() * square_tile<BM, 2>::PER_CU;
+    if (grid > resident) grid = resident >= 8 ? resident & ~7u : resident;
+  }
   hipLaunchKernelGGL(kern, dim3(grid), dim3(WM * WN * 64), lds, s, g, tiles_m, tiles_n);
   PT_HIP_CHECK(hipGetLastError());
   return 1;

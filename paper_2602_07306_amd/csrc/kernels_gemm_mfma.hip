@@ -1,5 +1,7 @@
 // Chooses the tile configuration of the MFMA GEMM family by shape and dispatches to the kernels, which are
 // instantiated per epilogue in kernels_gemm_mfma_{store,residual,swiglu,qkv_a..d,qkv_rows_a..c}.hip from gemm_mfma_impl.h.
+#include <algorithm>
+
 #include "pt_device.h"
 
 template <int EPI, int CFG>
@@ -42,23 +44,25 @@ static bool cfg_fits(const pt_gemm_args& g, int cfg) {
   return true;
 }
 
-// Expected time in us of a GEMM on tile configuration 0 (256 x 256), 4 (128 x 256) or 2 (128 x 128) with its K cut into
-// `slices`.  A launch runs in rounds of one tile per compute unit.  The fixed part of configuration 2 counts once: its LDS
-// leaves room for a second workgroup, so the fills and epilogues of later rounds hide behind the other's K loop.  What
-// bounds a round is the latency of the K loop's loads, hence a fixed part and a part per K step of 64, fitted on
-// one-round launches at K = 1024 and 4096 (4 tracks, 16 to 64 workgroups): 33.8 / 82, 24.4 / 59.6 and 17.9 / 44.3 us.
-// It orders the three correctly at M = 96 to 4096 of the Mid, Large and one-GPU-share shapes: e.g. 4 tracks x 1024 x 1024 rows,
-// K = 4096: 88 / 65 / 49 us; 8 tracks x 256 x 2048, K = 8192: 172 / 120 / 91; 4 tracks x 1024 x 3072, K = 1024:
-// 40 / 48 / 41; 4 tracks x 4096 x 8192, K = 1024: 271 / 328 / 304.
-static double tile_us(const pt_gemm_args& g, int cfg, int slices) {
+// Expected time in us of a GEMM on tile configuration 0 (256 x 256), 2 (128 x 128) or 4 (128 x 256).  0 and 4 run in
+// rounds of one tile per compute unit, each with an epilogue and a part per K step of 64, both longer the more of the chip
+// works (`full`); the tiles of 2 share their unit two at a time.  Fitted inside the Mid model (4 tracks, K = 1024 and 4096;
+// us, measured 0 / 2): gate/up 100 rows 30 / 20, 512 33 / 42, 600 50 / 50, 1000 56 / 73, 4096 202 / 271; QKV 512 30 / 27, 1000
+// 36 / 41, 1300 58 / 51, 4096 88 / 125; out 1000 39 / 22, 3000 50 / 51, 4096 56 / 68; down 1000 84 / 46, 2000 93 / 76, 4096
+// 114 / 155; head 300 41 / 44, 1000 72 / 98.  It orders them correctly there and for Large (8 tracks, 512 rows: gate/up
+// 188 / 282, out 61 / 55) and the one-GPU share (512 rows: gate/up 325 / 441, down 484 / 281).  4 wins where one round of it
+// takes a residual GEMM that leaves 0 half empty and fills 2 twice (Mid down 1300 rows 65 against 84 / 75, Large down 512
+// 137 against 171 / 170) and for QKV of few rows with heads of 128, too wide for a wavefront of 2 (Large 96 rows 51 / 57).
+static double tile_us(const pt_gemm_args& g, int cfg) {
   const int bm = cfg == 0 ? 256 : 128, bn = cfg == 2 ? 128 : 256;
-  const int64_t tiles = (int64_t)((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn) * g.batch * slices;
-  const double steps = (double)g.K / (slices * GM_BK);
+  const int64_t tiles = (int64_t)((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn) * g.batch;
+  const double steps = (double)g.K / GM_BK;
   const int64_t n_cu = pt_device_cus();
-  const double rounds = (double)((tiles + n_cu - 1) / n_cu);
-  if (cfg == 0) return rounds * (16.7 + 1.02 * steps);
-  if (cfg == 4) return rounds * (12.4 + 0.735 * steps);
-  return 9.5 + rounds * 0.585 * steps;
+  const double rounds = (double)((tiles + n_cu - 1) / n_cu), full = std::min(1.0, (double)tiles / n_cu);
+  const bool res = g.epi == EPI_RESIDUAL, swiglu = g.epi == EPI_SWIGLU, qkv = g.epi == EPI_QKV;
+  if (cfg == 0) return 8.0 + rounds * ((res ? 10.6 + 18.0 * full : swiglu ? 5.0 : 9.0) + (0.9 + 0.3 * full) * steps);
+  if (cfg == 4) return rounds * (12.4 + (res ? 6.0 + 10.0 * full : 0.0) + 0.735 * steps) * (rounds > 1 ? 1.13 : 1.0);
+  return 10.0 + rounds * ((res ? 5.3 : swiglu ? 0.5 : qkv ? 1.5 : 4.3) + 0.48 * steps);
 }
 
 // Grouped GEMM.  Above 32 rows in an average group: the largest tile, also where a group fills a small part of it.  Group
@@ -103,10 +107,13 @@ static int choose_cfg(const pt_gemm_args& g) {
       if (cfg_fits(g, *c)) return *c;
     return -1;
   }
+  // One tile of rows and many rounds of 2: the weights' way from HBM is the time, and 4 has most of them in flight (gate/up of
+  // Large: 96 rows 109 us against 121 on 2 and 114 on 0, 128 rows 112 against 121 and 119).
+  if (g.M <= 128 && (int64_t)((g.N + 127) / 128) * g.batch >= 4 * (int64_t)pt_device_cus() && cfg_fits(g, 4)) return 4;
   int best = -1;
   double best_us = 1e30;
   for (int cfg : {0, 4, 2}) {
-    const double us = cfg_fits(g, cfg) ? tile_us(g, cfg, 1) : 1e30;
+    const double us = cfg_fits(g, cfg) ? tile_us(g, cfg) : 1e30;
     if (us < best_us) { best_us = us; best = cfg; }
   }
   return best;
@@ -129,15 +136,29 @@ int pt_gemm_mfma_fold_parts(const pt_gemm_args& g) {
 // 4 TB/s.  Measured, out + down projection in us without / with slices: Mid (4 tracks, width 1024) 128 rows 17.7 + 44.5
 // / 12.0 + 18.3, 256 rows 17.9 + 44.3 / 18.3 + 20.0; Large (8 x 2048) 96 rows 31.6 + 84.4 / 23.0 + 59.4; one-GPU share
 // (1 x 8192) 128 rows 80.9 + 283 / 41.7 + 102; the normalising kernel takes 1 to 9 us more.
+// What bounds a slice is the latency of its few K steps' weights on their way from HBM, hence estimates of their own.
+static double slice_us(const pt_gemm_args& g, int cfg, int slices) {
+  const int bm = cfg == 0 ? 256 : 128, bn = cfg == 2 ? 128 : 256;
+  const int64_t tiles = (int64_t)((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn) * g.batch * slices;
+  const double steps = (double)g.K / (slices * GM_BK);
+  const int64_t n_cu = pt_device_cus();
+  const double rounds = (double)((tiles + n_cu - 1) / n_cu);
+  if (cfg == 0) return rounds * (16.7 + 1.02 * steps);
+  if (cfg == 4) return rounds * (12.4 + 0.735 * steps);
+  return 9.5 + rounds * 0.585 * steps;
+}
+
 int pt_gemm_mfma_ksplit(const pt_gemm_args& g) {
   const int cfg = choose_cfg(g);
   if (cfg < 0 || g.epi != EPI_RESIDUAL || g.blk_group || !g.sk_part || ((uintptr_t)g.sk_part & 15) || pt_tune_gemm_cfg >= 0) return 1;
-  const double slice_us = (double)g.batch * g.M * g.N * 8.0 / 4e6;   // written and read once
-  double best_us = cfg == 0 || cfg == 4 || cfg == 2 ? tile_us(g, cfg, 1) : 1e30;
+  const double traffic_us = (double)g.batch * g.M * g.N * 8.0 / 4e6;   // a slice written and read once
+  double best_us = 1e30;
+  if (g.M > 64)
+    for (int c : {0, 4, 2}) best_us = std::min(best_us, slice_us(g, c, 1));
   int best = 1;
   for (int slices = 2; slices <= 16; slices *= 2) {
     if (g.K % (slices * 2 * GM_BK) || (int64_t)slices * g.batch * g.M * g.N > g.sk_part_floats) break;
-    const double us = tile_us(g, 2, slices) + slices * slice_us;
+    const double us = slice_us(g, 2, slices) + slices * traffic_us;
     if (us < 0.9 * best_us) { best_us = us; best = slices; }
   }
   return best;

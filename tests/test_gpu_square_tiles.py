@@ -1,0 +1,43 @@
+"""GPU parity of the square GEMM tiles (256 x 256 and 128 x 128), each forced for every GEMM that it covers: rows around the
+tiles' edges, the shortest K (two and four K steps of 64), K that is no multiple of four steps, a workgroup with several
+tiles of a launch, aligned and odd positions, both head widths, grouped KV heads."""
+import pytest
+
+from paper_2602_07306_amd import inputs as I
+from tests.helpers import BF16_TOL, assert_close, oracle_prefill, path_counts, small_bf16_config
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("tile", [0, 2])
+@pytest.mark.parametrize("B,S,d_model,heads,kv_heads,hd,d_ffn", [
+    (1, 65, 128, 2, 2, 64, 128),        # two K steps everywhere; one tile of rows, nearly half empty
+    (1, 127, 256, 4, 2, 64, 384),       # four and six K steps, grouped heads
+    (2, 128, 128, 2, 2, 64, 640),       # 256 rows: the tiles are full
+    (1, 257, 256, 2, 2, 128, 512),      # one row in the second tile, heads of 128, odd positions
+    (3, 96, 384, 4, 4, 128, 256),       # 32-row blocks, K of six steps
+    (2, 1056, 128, 2, 2, 64, 4096),     # more tiles than workgroups, the last tile of rows a quarter full
+    (1, 2111, 256, 2, 1, 128, 2048),    # the same with odd positions and one KV head
+])
+def test_square_tiles(tile, B, S, d_model, heads, kv_heads, hd, d_ffn):
+    from paper_2602_07306_amd import binding as PB
+    cfg = small_bf16_config(n_layers=2, block_depth=1, d_model=d_model, n_heads=heads, n_kv_heads=kv_heads, head_dim=hd,
+                            d_ffn=d_ffn, vocab=512, max_batch=B, max_seq=S)
+    W = I.make_weights(cfg, 43)
+    tokens = I.make_tokens(43, B, S, cfg.vocab)
+    ref, _ = oracle_prefill(cfg, W, tokens)
+    model = PB.PTModel(cfg)
+    model.pt_init_weights(43)
+    PB.pt_set_tuning(PB.PT_TUNE_GEMM_TILE_CONFIG, tile)
+    try:
+        model.pt_profile_reset()
+        lg, hid = model.pt_prefill(torch.from_numpy(tokens).cuda(), logits_mode=PB.PT_LOGITS_ALL, want_hidden=True)
+        torch.cuda.synchronize()
+        counts = path_counts(model)
+    finally:
+        PB.pt_set_tuning(PB.PT_TUNE_GEMM_TILE_CONFIG, -1)
+    assert counts["gemm_gateup"][1] == counts["gemm_down"][1] == counts["gemm_out"][1] == cfg.n_layers, counts
+    assert_close(lg.cpu().numpy().reshape(B, S, -1), ref["logits"], BF16_TOL, "logits")
+    assert_close(hid.cpu().numpy(), ref["hidden"], BF16_TOL, "hidden")
+    model.close()
