@@ -12,7 +12,9 @@ __device__ __forceinline__ float4 load4(const bf16_t* p) {
 // VEC: four elements per load, the loads of a key row (and of 16 keys of V^T) in flight together, and two groups of
 // keys side by side where a head is at most 32 wide (hd % 4 == 0, pointers aligned).  The loop of single loads waits
 // for memory once per key: one row of the Tiny model (32 to 40 keys, head width 32) 8.6 us before, 5.3 now.
-template <typename T, bool VEC>
+// NARROW (VEC, heads of at most 32): what bounds it is one load's latency after the other, so a chunk's keys, its values
+// and q are requested together.
+template <typename T, bool VEC, bool NARROW>
 __global__ void __launch_bounds__(64) attn_generic_kernel(pt_attn_args a) {
   __shared__ __attribute__((aligned(16))) float qs[256];
   const int lane = threadIdx.x;
@@ -34,15 +36,45 @@ __global__ void __launch_bounds__(64) attn_generic_kernel(pt_attn_args a) {
   const T* Vt = (const T*)a.vc + hidx * ((int64_t)hd * a.s_pad);
   const int64_t qoff = t * a.q_bstride + (int64_t)m * a.H * hd + head * hd;
   const T* q = (const T*)a.q + qoff;
-  for (int e = lane; e < hd; e += 64) qs[e] = elem<T>::ld(q + e);
-  __syncthreads();
+  float q_mine = 0.f;
+  if constexpr (NARROW) {
+    if (lane < hd) q_mine = elem<T>::ld(q + lane);
+  } else {
+    for (int e = lane; e < hd; e += 64) qs[e] = elem<T>::ld(q + e);
+    __syncthreads();
+  }
   const float scale = 1.0f / sqrtf((float)hd);
   float mrun = -INFINITY, lsum = 0.f;
   float acc[4] = {0.f, 0.f, 0.f, 0.f};
   for (int base = 0; base < nkeys; base += 64) {
     const int key = base + lane;
     float s = -INFINITY;
-    if (key < nkeys) {
+    const int nk = min(64, nkeys - base);
+    float4 kv[NARROW ? 8 : 1], vv[NARROW ? 8 : 1];
+    (void)kv; (void)vv;
+    if constexpr (NARROW) {
+      // lane: head-dim index lane % 32 of the values at positions 8 i + 4 * (lane / 32) .. + 3; the 64 positions of a chunk
+      // lie inside the cache row.  Lanes past the last key or the head's width repeat the last one.
+      const T* kr = K + (int64_t)min(key, nkeys - 1) * hd;
+      const T* vr = Vt + (int64_t)min(lane & 31, hd - 1) * a.s_pad + base + 4 * (lane >> 5);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) kv[i] = load4(kr + min(4 * i, hd - 4));
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        if (8 * i < nk) vv[i] = load4(vr + 8 * i);
+      if (base == 0) {
+        if (lane < hd) qs[lane] = q_mine;
+        __syncthreads();
+      }
+      float4 d = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        if (4 * i < hd) {
+          const float4 q4 = *(const float4*)(qs + 4 * i);
+          d.x = fmaf(q4.x, kv[i].x, d.x); d.y = fmaf(q4.y, kv[i].y, d.y); d.z = fmaf(q4.z, kv[i].z, d.z); d.w = fmaf(q4.w, kv[i].w, d.w);
+        }
+      if (key < nkeys) s = ((d.x + d.y) + (d.z + d.w)) * scale;
+    } else if (key < nkeys) {
       const T* kr = K + (int64_t)key * hd;
       float dot = 0.f;
       if constexpr (VEC) {
@@ -63,18 +95,27 @@ __global__ void __launch_bounds__(64) attn_generic_kernel(pt_attn_args a) {
     const float corr = expf(mrun - mnew);   // 0 on the first chunk
     lsum = lsum * corr + wave_sum(p);
     mrun = mnew;
-    const int nk = min(64, nkeys - base);
 #pragma unroll
     for (int i = 0; i < 4; ++i) acc[i] *= corr;
-    if constexpr (VEC) {
-      const int groups = hd <= 32 ? 2 : 1, e0 = hd <= 32 ? lane & 31 : lane, grp = hd <= 32 ? lane >> 5 : 0;
+    if constexpr (NARROW) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        if (8 * i < nk) {                               // wave-uniform
+          const int kk = 8 * i + 4 * (lane >> 5);
+          const float p0 = __shfl(p, kk, 64), p1 = __shfl(p, kk + 1, 64), p2 = __shfl(p, kk + 2, 64), p3 = __shfl(p, kk + 3, 64);
+          // positions that no token has written may hold anything, and 0 * NaN is not 0
+          acc[0] = fmaf(p0, kk < nk ? vv[i].x : 0.f, acc[0]);
+          acc[0] = fmaf(p1, kk + 1 < nk ? vv[i].y : 0.f, acc[0]);
+          acc[0] = fmaf(p2, kk + 2 < nk ? vv[i].z : 0.f, acc[0]);
+          acc[0] = fmaf(p3, kk + 3 < nk ? vv[i].w : 0.f, acc[0]);
+        }
+    } else if constexpr (VEC) {
 #pragma unroll 4
-      for (int k4 = 0; k4 < nk; k4 += 4 * groups) {   // the same trip count in both groups: the shuffles need every lane
-        const int kk = k4 + 4 * grp;                  // at most 60: the 64 positions of a chunk lie inside the cache row
+      for (int kk = 0; kk < nk; kk += 4) {            // at most 60: the 64 positions of a chunk lie inside the cache row
         const float p0 = __shfl(p, kk, 64), p1 = __shfl(p, kk + 1, 64), p2 = __shfl(p, kk + 2, 64), p3 = __shfl(p, kk + 3, 64);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          const int e = e0 + 64 * i;
+          const int e = lane + 64 * i;
           if (e < hd) {
             const float4 v = load4(Vt + (int64_t)e * a.s_pad + base + kk);
             // positions that no token has written may hold anything, and 0 * NaN is not 0
@@ -97,7 +138,7 @@ __global__ void __launch_bounds__(64) attn_generic_kernel(pt_attn_args a) {
   }
   T* o = (T*)a.o + qoff;
   const float inv = 1.0f / lsum;
-  if (VEC && hd <= 32) acc[0] += __shfl_xor(acc[0], 32, 64);
+  if (NARROW) acc[0] += __shfl_xor(acc[0], 32, 64);   // positions 0-3 and 4-7 of every eight
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int e = lane + 64 * i;
@@ -112,11 +153,13 @@ int pt_launch_attn_generic(const pt_attn_args& a, hipStream_t s) {
   dim3 grid((unsigned)rows, (unsigned)a.H, (unsigned)a.n_tracks);
   const bool vec = !((a.hd | a.s_pad) & 3) && !(a.kv_head_elems & 3) && !(((uintptr_t)a.kc | (uintptr_t)a.vc) & 15);
   if (a.dtype == PT_F32) {
-    if (vec) hipLaunchKernelGGL((attn_generic_kernel<float, true>), grid, dim3(64), 0, s, a);
-    else hipLaunchKernelGGL((attn_generic_kernel<float, false>), grid, dim3(64), 0, s, a);
+    if (vec && a.hd <= 32) hipLaunchKernelGGL((attn_generic_kernel<float, true, true>), grid, dim3(64), 0, s, a);
+    else if (vec) hipLaunchKernelGGL((attn_generic_kernel<float, true, false>), grid, dim3(64), 0, s, a);
+    else hipLaunchKernelGGL((attn_generic_kernel<float, false, false>), grid, dim3(64), 0, s, a);
   } else {
-    if (vec) hipLaunchKernelGGL((attn_generic_kernel<bf16_t, true>), grid, dim3(64), 0, s, a);
-    else hipLaunchKernelGGL((attn_generic_kernel<bf16_t, false>), grid, dim3(64), 0, s, a);
+    if (vec && a.hd <= 32) hipLaunchKernelGGL((attn_generic_kernel<bf16_t, true, true>), grid, dim3(64), 0, s, a);
+    else if (vec) hipLaunchKernelGGL((attn_generic_kernel<bf16_t, true, false>), grid, dim3(64), 0, s, a);
+    else hipLaunchKernelGGL((attn_generic_kernel<bf16_t, false, false>), grid, dim3(64), 0, s, a);
   }
   PT_HIP_CHECK(hipGetLastError());
   return PT_OK;

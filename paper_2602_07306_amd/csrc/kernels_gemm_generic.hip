@@ -87,7 +87,7 @@ __global__ void __launch_bounds__(256) gemm_generic_kernel(pt_gemm_args g) {
       break;
     case EPI_QKV:
       if (n0 < (g.H + g.Hkv) * g.hd) {
-        epi_rope_pair<T>(g, b, m, n0, acc0, acc1);
+        epi_rope_pair<T>(g, b, m, n0, acc0, acc1, epi_rope_entry(g, m, n0));
       } else {
         epi_v<T>(g, b, m, n0, acc0);
         epi_v<T>(g, b, m, n1, acc1);
@@ -96,12 +96,28 @@ __global__ void __launch_bounds__(256) gemm_generic_kernel(pt_gemm_args g) {
   }
 }
 
+// Sum over the 64 lanes, in every lane: prefix sums inside rows of 16 lanes, carried from row to row (no LDS).
+__device__ __forceinline__ float wave_sum_dpp(float x) {
+#define PT_DPP_ADD(ctrl, rows) \
+  x += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), ctrl, rows, 0xf, false))
+  PT_DPP_ADD(0x111, 0xf);   // row_shr:1
+  PT_DPP_ADD(0x112, 0xf);   // row_shr:2
+  PT_DPP_ADD(0x114, 0xf);   // row_shr:4
+  PT_DPP_ADD(0x118, 0xf);   // row_shr:8
+  PT_DPP_ADD(0x142, 0xa);   // row_bcast:15 into rows 1 and 3
+  PT_DPP_ADD(0x143, 0xc);   // row_bcast:31 into rows 2 and 3
+#undef PT_DPP_ADD
+  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), 63));
+}
+
 // fp32, few rows: one wavefront per pair of output columns and MR rows, lanes along K.  What bounds these launches is
 // latency: the kernel above walks K in steps of 32 with two barriers each, about 1.1 us a step; here all loads of
 // 256 elements of K are in flight at once and the lanes are folded at the end.  One row of the Tiny model, event to
 // event with 6.3 us of overhead, K = 128 / 512: 9.5 / 24.5 us before, 6.4 / 6.4 now; fp32 at 4 tracks, width 1024: QKV, out,
 // gate/up, down 63 / 52 / 84 / 188 us before, 15 / 8 / 27 / 18 now.
-template <int MR>
+// NORM: the operand is RMSNorm(norm_src) * norm_gain, formed on the way (the row's 1/rms multiplies the finished sums),
+// which saves the launch in front.  What the epilogue reads (residual values, rotary table) is loaded ahead of the sums.
+template <int MR, bool NORM>
 __global__ void __launch_bounds__(256) gemm_rows_kernel(pt_gemm_args g) {
   const int lane = threadIdx.x & 63;
   const int p = blockIdx.x * 4 + (threadIdx.x >> 6), m0 = blockIdx.y * MR, b = blockIdx.z;
@@ -110,45 +126,69 @@ __global__ void __launch_bounds__(256) gemm_rows_kernel(pt_gemm_args g) {
   pair_columns(g, p, &n0, &n1);
   const float* w0p = (const float*)g.W + b * g.w_bstride + (int64_t)n0 * g.ldb;
   const float* w1p = (const float*)g.W + b * g.w_bstride + (int64_t)n1 * g.ldb;
+  const float* a_first = NORM ? g.norm_src + b * g.norm_bstride : (const float*)g.A + b * g.a_bstride;
+  const float* gain = NORM ? g.norm_gain + b * g.norm_gbstride : nullptr;
   const float* ap[MR];
 #pragma unroll
-  for (int r = 0; r < MR; ++r) ap[r] = (const float*)g.A + b * g.a_bstride + (int64_t)min(m0 + r, g.M - 1) * g.lda;
-  float acc0[MR], acc1[MR];
+  for (int r = 0; r < MR; ++r) ap[r] = a_first + (int64_t)min(m0 + r, g.M - 1) * g.lda;
+  const int m = m0 + lane;                           // lane r finishes row m0 + r
+  const bool mine = lane < MR && m < g.M;
+  const bool rotated = g.epi == EPI_QKV && n0 < (g.H + g.Hkv) * g.hd;
+  float2 ahead = make_float2(0.f, 0.f);
+  if (mine) {
+    if (g.epi == EPI_RESIDUAL) {                      // n1 = n0 + 1; single loads: nothing promises their alignment
+      const float* r = g.res + b * g.res_bstride + (int64_t)m * g.ldo + n0;
+      ahead = make_float2(r[0], r[1]);
+    } else if (rotated) {
+      ahead = epi_rope_entry(g, m, n0);
+    }
+  }
+  float acc0[MR], acc1[MR], ss[MR];
 #pragma unroll
-  for (int r = 0; r < MR; ++r) acc0[r] = acc1[r] = 0.f;
+  for (int r = 0; r < MR; ++r) acc0[r] = acc1[r] = ss[r] = 0.f;
 #pragma unroll 2
   for (int k = lane * 4; k < g.K; k += 256) {
     const float4 w0 = *(const float4*)(w0p + k), w1 = *(const float4*)(w1p + k);
+    float4 gn = make_float4(1.f, 1.f, 1.f, 1.f);
+    if constexpr (NORM) gn = *(const float4*)(gain + k);
 #pragma unroll
     for (int r = 0; r < MR; ++r) {
-      const float4 a = *(const float4*)(ap[r] + k);
+      float4 a = *(const float4*)(ap[r] + k);
+      if constexpr (NORM) {
+        ss[r] = fmaf(a.w, a.w, fmaf(a.z, a.z, fmaf(a.y, a.y, fmaf(a.x, a.x, ss[r]))));
+        a.x *= gn.x; a.y *= gn.y; a.z *= gn.z; a.w *= gn.w;
+      }
       acc0[r] = fmaf(a.w, w0.w, fmaf(a.z, w0.z, fmaf(a.y, w0.y, fmaf(a.x, w0.x, acc0[r]))));
       acc1[r] = fmaf(a.w, w1.w, fmaf(a.z, w1.z, fmaf(a.y, w1.y, fmaf(a.x, w1.x, acc1[r]))));
     }
   }
-  float lo = 0.f, hi = 0.f;   // lane r finishes row m0 + r
+  float lo = 0.f, hi = 0.f;
 #pragma unroll
   for (int r = 0; r < MR; ++r) {
-    const float s0 = wave_sum(acc0[r]), s1 = wave_sum(acc1[r]);
+    float s0 = wave_sum_dpp(acc0[r]), s1 = wave_sum_dpp(acc1[r]);
+    if constexpr (NORM) {
+      const float inv = 1.0f / sqrtf(wave_sum_dpp(ss[r]) / (float)g.K + g.norm_eps);
+      s0 *= inv;
+      s1 *= inv;
+    }
     if (lane == r) { lo = s0; hi = s1; }
   }
-  const int m = m0 + lane;
-  if (lane >= MR || m >= g.M) return;
+  if (!mine) return;
   switch (g.epi) {
     case EPI_STORE_F32:
       epi_store_f32<float>(g, b, m, n0, lo);
       epi_store_f32<float>(g, b, m, n1, hi);
       break;
     case EPI_RESIDUAL:
-      epi_residual<float>(g, b, m, n0, lo);
-      epi_residual<float>(g, b, m, n1, hi);
+      epi_store_f32<float>(g, b, m, n0, ahead.x + lo);
+      epi_store_f32<float>(g, b, m, n1, ahead.y + hi);
       break;
     case EPI_SWIGLU:
       epi_swiglu<float>(g, b, m, p, lo, hi);
       break;
     case EPI_QKV:
-      if (n0 < (g.H + g.Hkv) * g.hd) {
-        epi_rope_pair<float>(g, b, m, n0, lo, hi);
+      if (rotated) {
+        epi_rope_pair<float>(g, b, m, n0, lo, hi, ahead);
       } else {
         epi_v<float>(g, b, m, n0, lo);
         epi_v<float>(g, b, m, n1, hi);
@@ -163,9 +203,13 @@ __global__ void __launch_bounds__(256) gemm_rows_kernel(pt_gemm_args g) {
 static bool rows_covers(const pt_gemm_args& g) {
   const double wgs = (double)((g.N / 2 + 3) / 4) * ((g.M + 3) / 4) * g.batch;
   if (wgs * (2.0 + g.K / 400.0) >= 44.0 * g.K || g.M > 4 * 65535) return false;
-  return g.dtype == PT_F32 && !g.blk_group && !g.a_rows && !((g.K | g.lda | g.ldb) & 3) &&
-         !((g.a_bstride | g.w_bstride) & 3) && !(((uintptr_t)g.A | (uintptr_t)g.W) & 15);
+  if (g.dtype != PT_F32 || g.blk_group || g.a_rows || ((g.K | g.lda | g.ldb) & 3) || (g.w_bstride & 3) || ((uintptr_t)g.W & 15)) return false;
+  // the caller's hidden states may lie anywhere: rows of norm_src are read with loads that need 4-byte alignment only
+  if (g.norm_src) return !(g.norm_gbstride & 3) && !((uintptr_t)g.norm_gain & 15);
+  return !(g.a_bstride & 3) && !((uintptr_t)g.A & 15);
 }
+
+bool pt_gemm_generic_fuses_norm(const pt_gemm_args& g) { return rows_covers(g) && g.epi != EPI_RESIDUAL; }
 
 int pt_launch_gemm_generic(const pt_gemm_args& g, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0 || g.batch <= 0) return PT_OK;
@@ -173,13 +217,18 @@ int pt_launch_gemm_generic(const pt_gemm_args& g, hipStream_t s) {
   if (rows_covers(g)) {
     const int mr = g.M == 1 ? 1 : 4;
     const dim3 rgrid((unsigned)((g.N / 2 + 3) / 4), (unsigned)((g.M + mr - 1) / mr), (unsigned)g.batch);
-    if (mr == 1)
-      hipLaunchKernelGGL(gemm_rows_kernel<1>, rgrid, dim3(256), 0, s, g);
+    if (mr == 1 && g.norm_src)
+      hipLaunchKernelGGL((gemm_rows_kernel<1, true>), rgrid, dim3(256), 0, s, g);
+    else if (mr == 1)
+      hipLaunchKernelGGL((gemm_rows_kernel<1, false>), rgrid, dim3(256), 0, s, g);
+    else if (g.norm_src)
+      hipLaunchKernelGGL((gemm_rows_kernel<4, true>), rgrid, dim3(256), 0, s, g);
     else
-      hipLaunchKernelGGL(gemm_rows_kernel<4>, rgrid, dim3(256), 0, s, g);
+      hipLaunchKernelGGL((gemm_rows_kernel<4, false>), rgrid, dim3(256), 0, s, g);
     PT_HIP_CHECK(hipGetLastError());
     return PT_OK;
   }
+  if (g.norm_src) return pt_set_error(PT_ERR_HIP, "a GEMM that was to form its own normalised operand was not taken by that kernel");
   dim3 grid((unsigned)((g.N / 2 + 15) / 16), (unsigned)((g.M + 15) / 16), (unsigned)g.batch);
   if (grid.y > 65535u) return pt_set_error(PT_ERR_INVALID_ARGUMENT, "generic GEMM: M too large");
   if (g.dtype == PT_F32)

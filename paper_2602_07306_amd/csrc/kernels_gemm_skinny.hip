@@ -747,6 +747,7 @@ static bool use_gemv(const pt_gemm_args& g) {
 }
 
 bool pt_gemm_fuses_norm(const pt_gemm_args& g) {
+  if (g.dtype == PT_F32) return pt_gemm_generic_fuses_norm(g);
   return skinny_covers(g) && use_gemv(g) && (g.epi == EPI_QKV || g.epi == EPI_SWIGLU) && g.lda == g.K;
 }
 

@@ -427,8 +427,7 @@ static int run_gemm(pt_handle* h, const pt_gemm_args& g_in, int cls) {
     int r = g.M <= 64 || g.n_groups > 0 ? pt_launch_gemm_skinny(g, false, h->stream) : 0;
     if (r < 0) return r;
     if (r > 0) { count_family(h, cls, r); return PT_OK; }
-    if (g.norm_src) return pt_set_error(PT_ERR_HIP, "a GEMM that was to form its own normalised operand was not taken by that kernel");
-    r = pt_launch_gemm_mfma(g, h->stream);
+    if (!g.norm_src) r = pt_launch_gemm_mfma(g, h->stream);   // the tile kernels do not form their operand
     if (r < 0) return r;
     if (r > 0) { count_family(h, cls, r); return PT_OK; }
   }
@@ -830,14 +829,6 @@ static int forward(pt_handle* h, const pt_workspace& w, const int32_t* dev_token
   if (logits_mode != PT_LOGITS_NONE && (dev_logits || dev_argmax)) {
     const int64_t lrows = logits_mode == PT_LOGITS_ALL ? (ragged_prefill ? rg->n_valid : rows) : B;
     const float* gf = (const float*)(h->w + l.off_gf);
-    if (ragged_prefill)   // the rows of the real tokens (all of them, or each sequence's last one), gathered by index
-      rc = pt_launch_rmsnorm_rows(merged, gf, abuf, c.dtype, lrows, 0, 0, logits_mode == PT_LOGITS_ALL ? rg->valid : rg->last,
-                                  (int32_t)d, c.rms_eps, st);
-    else if (logits_mode == PT_LOGITS_ALL)
-      rc = pt_launch_rmsnorm_rows(merged, gf, abuf, c.dtype, lrows, 1, 0, nullptr, (int32_t)d, c.rms_eps, st);
-    else
-      rc = pt_launch_rmsnorm_rows(merged, gf, abuf, c.dtype, lrows, S, S - 1, nullptr, (int32_t)d, c.rms_eps, st);
-    if (rc) return rc;
     float* lg = dev_logits;
     if (!lg) return pt_set_error(PT_ERR_NULL_POINTER, "argmax needs a logits buffer");
     pt_gemm_args g;
@@ -847,6 +838,23 @@ static int forward(pt_handle* h, const pt_workspace& w, const int32_t* dev_token
     g.M = (int32_t)lrows; g.N = c.vocab; g.K = (int32_t)d; g.batch = 1;
     g.dtype = c.dtype; g.epi = EPI_STORE_F32;
     g.out = lg; g.out_bstride = 0; g.ldo = c.vocab;
+    // a handful of fp32 rows that lie at one distance: the head's GEMM forms its own operand
+    if (c.dtype == PT_F32 && h->path == PT_PATH_AUTO && !ragged_prefill && (int64_t)S * d <= 0x7fffffff) {
+      pt_gemm_args p = g;
+      const bool all = logits_mode == PT_LOGITS_ALL;
+      p.norm_src = all ? merged : merged + (int64_t)(S - 1) * d; p.lda = (int32_t)(all ? d : (int64_t)S * d);
+      p.norm_gain = gf; p.norm_eps = c.rms_eps;
+      if (pt_gemm_fuses_norm(p)) g = p;
+    }
+    if (g.norm_src) rc = PT_OK;
+    else if (ragged_prefill)   // the rows of the real tokens (all of them, or each sequence's last one), gathered by index
+      rc = pt_launch_rmsnorm_rows(merged, gf, abuf, c.dtype, lrows, 0, 0, logits_mode == PT_LOGITS_ALL ? rg->valid : rg->last,
+                                  (int32_t)d, c.rms_eps, st);
+    else if (logits_mode == PT_LOGITS_ALL)
+      rc = pt_launch_rmsnorm_rows(merged, gf, abuf, c.dtype, lrows, 1, 0, nullptr, (int32_t)d, c.rms_eps, st);
+    else
+      rc = pt_launch_rmsnorm_rows(merged, gf, abuf, c.dtype, lrows, S, S - 1, nullptr, (int32_t)d, c.rms_eps, st);
+    if (rc) return rc;
     rc = run_gemm(h, g, PT_K_GEMM_HEAD);
     if (rc) return rc;
     if (dev_argmax) {

@@ -44,16 +44,20 @@ __device__ __forceinline__ void epi_swiglu(const pt_gemm_args& g, int b, int m, 
   elem<T>::st((T*)g.olp + b * g.olp_bstride + (int64_t)m * (g.N >> 1) + j, silu_f(gate) * up);
 }
 
+// cosine and sine for row m and the column pair of physical column n0 (q or k section, n0 % hd < hd/2)
+__device__ __forceinline__ float2 epi_rope_entry(const pt_gemm_args& g, int m, int n0) {
+  return ((const float2*)g.rope)[(int64_t)gemm_row_pos(g, m).pos * (g.hd >> 1) + n0 % g.hd];
+}
+
 // q or k section.  n0 = physical column of the low half (n0 % hd < hd/2); partner = n0 + hd/2.
 template <typename T>
-__device__ __forceinline__ void epi_rope_pair(const pt_gemm_args& g, int b, int m, int n0, float lo, float hi) {
+__device__ __forceinline__ void epi_rope_pair(const pt_gemm_args& g, int b, int m, int n0, float lo, float hi, float2 cs) {
   const int hq = g.H * g.hd, half = g.hd >> 1;
   const pt_rowpos rp = gemm_row_pos(g, m);
   const int seq = rp.seq, pos = rp.pos;
   const bool is_q = n0 < hq;
   const int c = is_q ? n0 : n0 - hq;
   const int head = c / g.hd, j = c - head * g.hd;
-  const float2 cs = ((const float2*)g.rope)[(int64_t)pos * half + j];
   const float rlo = lo * cs.x - hi * cs.y;
   const float rhi = hi * cs.x + lo * cs.y;
   if (is_q) {

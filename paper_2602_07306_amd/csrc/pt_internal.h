@@ -262,8 +262,11 @@ bool pt_gemm_mfma_covers(const pt_gemm_args& g);
 // instead of writing out = res + product; pt_launch_resnorm adds them up.
 int pt_launch_gemm_skinny(const pt_gemm_args& g, bool allow_split, hipStream_t s);
 int pt_gemm_skinny_ksplit(const pt_gemm_args& g);
-// True if pt_launch_gemm_skinny would run this problem (shape fields only) on the kernel that can form its A
-// operand from the fp32 residual stream (norm_* fields), which saves the RMSNorm launch in front of it.
+// True if this problem would run (shape fields only; norm_* or, in their place, A) on a kernel that can form its A operand
+// from the fp32 residual stream (norm_* fields), which saves the RMSNorm launch in front of it: the matrix-vector form of
+// pt_launch_gemm_skinny, or for fp32 the few-row form of pt_launch_gemm_generic (pt_gemm_generic_fuses_norm; its rows of
+// norm_src are lda apart).
+bool pt_gemm_generic_fuses_norm(const pt_gemm_args& g);
 bool pt_gemm_fuses_norm(const pt_gemm_args& g);
 
 // ---------------------------------------------------------------------------------------------
