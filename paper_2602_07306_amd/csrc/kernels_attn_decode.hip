@@ -12,6 +12,8 @@
 //            from LDS; each wavefront owns hd/4 rows and reduces across lanes once at the end.
 // With more than one split each workgroup writes (max, sum, unnormalised output) and a small kernel
 // combines the splits; with one split the normalised output is written directly.
+#include <algorithm>
+
 #include "pt_device.h"
 
 #define DEC_CHUNK 512          // positions one wavefront covers per step of phase 3 (64 lanes x 8)
@@ -409,6 +411,223 @@ __global__ void __launch_bounds__(256, HD == 64 ? 3 : 2) attn_decode_tiled_kerne
   }
 }
 
+// One wavefront per (track, sequence, KV head) and key range, for launches of a middling number of them.  The kernel above
+// has phases without loads in flight (a workgroup's first tile, the merge of its wavefronts), about two tiles' worth of
+// time; here nothing is merged and no wavefront waits for another.  Tiles of 64 keys go straight into the wavefront's own
+// LDS and are read into registers whole; the next tile's loads are issued before the first product.  The tile's rows are
+// whole cache lines: K [64 x HD], V^T [HD x 64 keys]; a cache row holds a multiple of 64 positions, so a tile never leaves
+// it.  MFMA layout, softmax state and partials as above.
+// What bounds it is HBM again, and past a thousand wavefronts their many streams get slower than the larger tiles above
+// (4 tracks x 32 sequences x 16 heads x 2048 keys 201 us against 197; tiles of 128 keys here 209).  us a launch with the
+// kernel above / with this one, hd = 128 (8 tracks, 2 or 4 KV heads): 64 heads x 2048 keys 34.3 / 27.4, 128 x 512 21.8 / 19.4,
+// 256 x 2048 67.7 / 60.2, 512 x 128 21.4 / 17.2, 512 x 512 47.7 / 34.2, 768 x 512 64.9 / 46.1, 1024 x 512 67.0 / 60.3,
+// 1024 x 4096 355 / 356, 2048 x 512 120 / 121; hd = 64 (4 tracks, 16 heads): 512 x 256 14.7 / 15.7, 512 x 512 26.1 / 22.5,
+// 1024 x 256 23.8 / 22.4, 1024 x 1024 60.0 / 56.4, 1024 x 4096 203 / 192, 1536 x 512 48.1 / 47.1, 4096 x 1024 207 / 217.
+template <int HD>
+__global__ void __launch_bounds__(64, HD == 64 ? 3 : 2) attn_decode_wave_kernel(const pt_attn_args a, int nsplit, int keys_per_split) {
+#if defined(__HIP_DEVICE_COMPILE__)   // the buffer types exist on the device only
+  constexpr int KS = HD / 16, HB = HD / 32, TK = 64;   // TK: keys of a tile
+  constexpr int KROW = HD * 2;                  // bytes of a key row
+  constexpr int KCH = KROW / 16;                // 16-byte chunks of it
+  constexpr int KRPI = 64 / KCH;                // key rows per load instruction
+  constexpr int VROW = TK * 2, VCH = VROW / 16, VRPI = 64 / VCH;   // the same of V^T rows (TK keys)
+  constexpr int NK = TK / KRPI, NV = HD / VRPI; // load instructions per tile
+  constexpr int NB = TK / 32, NU = TK / 16;     // blocks of 32 keys, operands of 16 keys
+  __shared__ __attribute__((aligned(1024))) char smem[TK * KROW + HD * VROW];
+  typedef __attribute__((address_space(3))) void* lptr_t;
+  const int lane = threadIdx.x, l32 = lane & 31, half = lane >> 5;
+  const int split = blockIdx.x, kvh = blockIdx.y;
+  const int t = blockIdx.z / a.B, seq = blockIdx.z - t * a.B;
+  const int G = a.H / a.Hkv;
+  // ragged batch: this sequence's own length, the same for every lane
+  const int nkeys = (a.row_map ? ((const __attribute__((address_space(4))) int32_t*)(const int32_t*)(a.row_map + seq))[1] : a.pos0) + 1;
+  const int k0 = split * keys_per_split;
+  const int k1 = min(nkeys, k0 + keys_per_split);
+  float* part0 = a.partials + (((int64_t)blockIdx.z * a.H + kvh * G) * nsplit + split) * (HD + 2);   // of the group's first head
+  if (k0 >= nkeys) {   // no key in this range: the neutral element of the combine
+    for (int e = lane; e < HD * G; e += 64) {
+      const int g = e / HD, r = e - g * HD;
+      float* part = part0 + (int64_t)g * nsplit * (HD + 2);
+      if (r == 0) { part[0] = -INFINITY; part[1] = 0.f; }
+      part[2 + r] = 0.f;
+    }
+    return;
+  }
+  const int64_t hidx = t * a.kv_bstride + seq * a.kv_seq_stride + kvh;
+  const int64_t qbase = t * a.q_bstride + (int64_t)seq * (a.H * HD) + (int64_t)kvh * G * HD;
+  auto kswz = [](int row) { return HD == 128 ? (row & 15) : ((row >> 1) & 7); };   // K rows of 256 or 128 bytes
+  auto vswz = [](int row) { return (row >> 1) & 7; };                             // V^T rows of 128 bytes
+  const __amdgpu_buffer_rsrc_t rk = __builtin_amdgcn_make_buffer_rsrc((bf16_t*)a.kc + hidx * a.kv_head_elems, 0, (uint32_t)(a.kv_head_elems * 2), 0x00020000);
+  const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc((bf16_t*)a.vc + hidx * ((int64_t)HD * a.s_pad), 0, (uint32_t)(HD * a.s_pad * 2), 0x00020000);
+  // Lane's row inside an instruction and its swizzled chunk.  The swizzle of a row 8 (or 4) further on: instruction i adds
+  // its rows to the ones below, which changes the swizzle by a constant that repeats after `period` instructions.
+  const int kr = lane / KCH, vr = lane / VCH;
+  constexpr int KP = 16 / KRPI, VP = 16 / VRPI;          // instructions after which the swizzle repeats
+  uint32_t k_off[KP], v_off[VP];
+#pragma unroll
+  for (int i = 0; i < KP; ++i) k_off[i] = kr * KROW + (((lane % KCH) ^ kswz(i * KRPI + kr)) * 16);
+#pragma unroll
+  for (int i = 0; i < VP; ++i) v_off[i] = vr * (uint32_t)(a.s_pad * 2) + (((lane % VCH) ^ vswz(i * VRPI + vr)) * 16);
+  char* kt = smem;
+  char* vt = smem + TK * KROW;
+  int v_step = VRPI * a.s_pad * 2;
+  auto load_k = [&](int kb) {
+    int at = kb * KROW;
+#pragma unroll
+    for (int i = 0; i < NK; ++i) {
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rk, (lptr_t)(kt + i * 1024), 16, k_off[i % KP], at, 0, 0);
+      at += KRPI * KROW;
+    }
+  };
+  auto load_v = [&](int kb) {
+    asm volatile("" : "+s"(v_step));   // opaque: its multiples would be kept in scalar registers instead of added up
+    int at = kb * 2;
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rv, (lptr_t)(vt + i * 1024), 16, v_off[i % VP], at, 0, 0);
+      at += v_step;
+    }
+  };
+  load_k(k0);
+  load_v(k0);
+  bf16x8_t qf[KS];   // B operand of S^T: query head l32 of the group (zero beyond G)
+#pragma unroll
+  for (int kk = 0; kk < KS; ++kk) {
+    dpk8 z;
+    z.u[0] = z.u[1] = z.u[2] = z.u[3] = 0u;
+    if (l32 < G) z.v = *(const bf16x8_t*)((const bf16_t*)a.q + qbase + (int64_t)l32 * HD + kk * 16 + half * 8);
+    qf[kk] = z.v;
+  }
+  const int krow = (l32 & ~12) | ((l32 & 4) << 1) | ((l32 & 8) >> 1);   // MFMA row r of S^T holds key pi(r)
+  const float c_log2 = 1.4426950408889634f / sqrtf((float)HD);
+  f32x16_t oacc[HB];
+#pragma unroll
+  for (int hb = 0; hb < HB; ++hb)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) oacc[hb][v] = 0.f;
+  float m_run = -INFINITY, l_run = 0.f;
+  for (int kb = k0; kb < k1; kb += TK) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the tile has landed; the wavefront is alone with it
+    const bool more = kb + TK < k1, tail = kb + TK > k1;
+    bf16x8_t kf[NB][KS];
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+      for (int kk = 0; kk < KS; ++kk) {
+        const int row = b * 32 + krow;
+        kf[b][kk] = *(const bf16x8_t*)(kt + row * KROW + (((2 * kk + half) ^ kswz(row)) * 16));
+      }
+    dpk8 vf[HB][NU];
+    auto read_v = [&] {
+#pragma unroll
+      for (int hb = 0; hb < HB; ++hb)
+#pragma unroll
+        for (int u = 0; u < NU; ++u) {
+          const int row = hb * 32 + l32;
+          vf[hb][u].v = *(const bf16x8_t*)(vt + row * VROW + (((2 * u + half) ^ vswz(row)) * 16));
+        }
+    };
+    if constexpr (HD == 64) read_v();            // at hd = 128 the registers hold the keys or the values
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    if (more) {
+      load_k(kb + TK);
+      if constexpr (HD == 64) load_v(kb + TK);
+    }
+    f32x16_t s[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) s[b][v] = 0.f;
+#pragma unroll
+      for (int kk = 0; kk < KS; ++kk) s[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[b][kk], qf[kk], s[b], 0, 0, 0);
+    }
+    if constexpr (HD != 64) {
+      read_v();
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      if (more) load_v(kb + TK);
+    }
+    // s[b], register v: key kb + 32 b + 16*(v/8) + 8*half + v%8, query head l32
+    if (tail) {
+#pragma unroll
+      for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+          if (kb + 32 * b + 16 * (v >> 3) + 8 * half + (v & 7) >= k1) s[b][v] = -INFINITY;
+      // cache bytes beyond the range are not data: zeroed so that 0 * x stays 0
+#pragma unroll
+      for (int hb = 0; hb < HB; ++hb)
+#pragma unroll
+        for (int u = 0; u < NU; ++u)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const int key = kb + 16 * u + 8 * half + 2 * j;
+            uint32_t w = vf[hb][u].u[j];
+            if (key >= k1) w &= 0xffff0000u;
+            if (key + 1 >= k1) w &= 0x0000ffffu;
+            vf[hb][u].u[j] = w;
+          }
+    }
+    float mx = -INFINITY;
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) mx = fmaxf(mx, s[b][v]);
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    const float m_new = fmaxf(m_run, mx);
+    const float corr = __builtin_amdgcn_exp2f((m_run - m_new) * c_log2);
+    const float mc = m_new * c_log2;
+    float psum = 0.f;
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        s[b][v] = __builtin_amdgcn_exp2f(fmaf(s[b][v], c_log2, -mc));
+        psum += s[b][v];
+      }
+    l_run = l_run * corr + psum;
+    m_run = m_new;
+    if (__any(corr != 1.0f)) {
+#pragma unroll
+      for (int hb = 0; hb < HB; ++hb)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) oacc[hb][v] *= corr;
+    }
+    dpk8 pf[NU];
+#pragma unroll
+    for (int u = 0; u < NU; ++u)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) pf[u].u[i] = pack_bf16x2(s[u >> 1][8 * (u & 1) + 2 * i], s[u >> 1][8 * (u & 1) + 2 * i + 1]);
+#pragma unroll
+    for (int hb = 0; hb < HB; ++hb)
+#pragma unroll
+      for (int u = 0; u < NU; ++u) oacc[hb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[hb][u].v, pf[u].v, oacc[hb], 0, 0, 0);
+  }
+  l_run += __shfl_xor(l_run, 32, 64);   // the half-waves of a query head hold disjoint keys with a common maximum
+  if (l32 < G) {
+    if (nsplit == 1) {
+      const float inv = 1.0f / l_run;
+      bf16_t* o = (bf16_t*)a.o + qbase + (int64_t)l32 * HD;
+#pragma unroll
+      for (int hb = 0; hb < HB; ++hb)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {   // rows hb*32 + 8 q + 4 half + 0..3
+          uint2 pk;
+          pk.x = pack_bf16x2(oacc[hb][4 * q] * inv, oacc[hb][4 * q + 1] * inv);
+          pk.y = pack_bf16x2(oacc[hb][4 * q + 2] * inv, oacc[hb][4 * q + 3] * inv);
+          *(uint2*)(o + hb * 32 + 8 * q + 4 * half) = pk;
+        }
+    } else {
+      float* part = part0 + (int64_t)l32 * nsplit * (HD + 2);
+      if (half == 0) { part[0] = m_run * c_log2; part[1] = l_run; }
+#pragma unroll
+      for (int hb = 0; hb < HB; ++hb)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) part[2 + hb * 32 + 8 * (v >> 2) + 4 * half + (v & 3)] = oacc[hb][v];
+    }
+  }
+#endif
+}
+
 template <int HD>
 static int launch_gqa(const pt_attn_args& a, dim3 grid, int nsplit, int kps, hipStream_t s) {
   constexpr int LDS = 2 * 128 * HD * 2;
@@ -429,6 +648,23 @@ int pt_launch_attn_decode(const pt_attn_args& a, hipStream_t s) {
   const int G = a.H / a.Hkv;
   if (G <= DEC_GMAX && (a.s_pad & 7) == 0) {   // measured at least as fast as the VALU kernel for G = 1 too
     const int64_t gbase = z * a.Hkv;
+    // 32-bit offsets inside a head's cache; whole tiles of 64 positions
+    const bool wave_fits = a.kv_head_elems * 2 < ((int64_t)1 << 31) && (int64_t)a.hd * a.s_pad * 2 < ((int64_t)1 << 31) &&
+                           a.kv_head_elems % (64 * a.hd) == 0;
+    if (wave_fits && gbase <= 1024 && (a.hd == 128 ? gbase >= 64 : gbase >= 512 && (nkeys >= 384 || gbase == 1024))) {
+      // two wavefronts per compute unit are enough; fewer heads are split into ranges of at least 256 keys
+      int ns = a.hd == 128 ? (int)std::max<int64_t>(1, std::min<int64_t>(512 / gbase, (nkeys + 255) / 256)) : 1;
+      ns = std::min(ns, a.max_splits);
+      const int kps = ((nkeys + ns - 1) / ns + 63) / 64 * 64;
+      ns = (nkeys + kps - 1) / kps;          // no empty range
+      const dim3 grid((unsigned)ns, (unsigned)a.Hkv, (unsigned)z);
+      if (a.hd == 64) hipLaunchKernelGGL(attn_decode_wave_kernel<64>, grid, dim3(64), 0, s, a, ns, kps);
+      else hipLaunchKernelGGL(attn_decode_wave_kernel<128>, grid, dim3(64), 0, s, a, ns, kps);
+      if (ns > 1)
+        hipLaunchKernelGGL(attn_decode_combine_kernel, dim3((unsigned)a.H, (unsigned)z), dim3(64), 0, s, a, ns);
+      PT_HIP_CHECK(hipGetLastError());
+      return 1;
+    }
     int nsplit = (int)((1024 + gbase - 1) / gbase);
     const int by_len = (nkeys + 511) / 512;
     if (nsplit > by_len) nsplit = by_len;
