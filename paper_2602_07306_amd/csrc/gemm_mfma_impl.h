@@ -1076,9 +1076,10 @@ static int launch_cfg(const pt_gemm_args& g, hipStream_t s) {
   unsigned grid = (unsigned)total;
   if constexpr (SQUARE && BM == 128) {
     // Four K steps of loads in flight, one workgroup per compute unit, instead of two with two steps each: where tiles
-    // leave no second workgroup (us, two steps / four: 4 tracks x 300 rows x 1024, K = 4096 33.7 / 29.1; 8 x 256 x 2048,
-    // K = 8192 112 / 97), and where one tile covers the rows, so that the weights' way from HBM is the time and K is not
-    // long enough to hide the tiles' ends (8 tracks x 96 rows x 16384: K = 2048 129 / 124, but K = 8192 176 / 195).
+    // leave no second workgroup (us inside the Mid model, two steps / four: 100 rows, QKV 20.7 / 18.6, gate/up 22.2 / 20.2,
+    // K slices of down 20.0 / 18.3; 4 tracks x 300 rows x 1024, K = 4096 33.7 / 29.1), and where one tile covers the rows, so
+    // that the weights' way from HBM is the time and K is not long enough to hide the tiles' ends (8 tracks x 96 rows x
+    // 16384: K = 2048 129 / 124, but K = 8192 176 / 195).
     if ((total <= pt_device_cus() || (tiles_m == 1 && g.K < 4096)) && g.K >= 4 * BK) {
       auto deep = gemm_tile_deep_kernel<BM, 4, EPI>;
       PT_SET_MAX_LDS_ONCE(deep, (square_tile<BM, 4>::LDS));

@@ -380,29 +380,28 @@ __device__ __forceinline__ void square_tile_run(int tiles_m, int tiles_n) {
   auto SWZ = [](int row) { return (row >> 1) & 7; };
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
-  int total, KT;                                          // tiles; K steps: even, >= 2
+  const pt_gemm_args& g0 = gemm_args_again();
+  // what the first tile's loads need, requested at once instead of one after the other on the way there
+  asm volatile("" ::"s"(g0.A), "s"(g0.W), "s"(g0.a_bstride), "s"(g0.w_bstride), "s"(g0.lda), "s"(g0.ldb), "s"(g0.M), "s"(g0.N), "s"(g0.K),
+               "s"(g0.batch), "s"(g0.blk_group), "s"(g0.a_rows), "s"(g0.k_tracks), "s"(tiles_m), "s"(tiles_n));
+  const int total = tiles_m * tiles_n * g0.batch;
+  const int KT = g0.K / BK;                               // K steps: even, >= 2
 
   // Loads: an instruction moves 8 rows of 128 bytes; this lane row lane / 8 and logical chunk (lane % 8) ^ swizzle.  Rows
   // and columns past the matrix are past the end of the buffer and read as zero.
   uint32_t a_voff[T], w_voff[T];
-  {
-    const pt_gemm_args& g = gemm_args_again();
-    total = tiles_m * tiles_n * g.batch;
-    KT = g.K / BK;
 #pragma unroll
-    for (int i = 0; i < T; ++i) {
-      const int row = (wave * T + i) * 8 + (lane >> 3);
-      const int ch = ((lane & 7) ^ SWZ(row)) * 8;
-      a_voff[i] = (uint32_t)(row * g.lda + ch) * 2;
-      w_voff[i] = (uint32_t)(row * g.ldb + ch) * 2;
-    }
+  for (int i = 0; i < T; ++i) {
+    const int row = (wave * T + i) * 8 + (lane >> 3);
+    const int ch = ((lane & 7) ^ SWZ(row)) * 8;
+    a_voff[i] = (uint32_t)(row * g0.lda + ch) * 2;
+    w_voff[i] = (uint32_t)(row * g0.ldb + ch) * 2;
   }
   struct place {
     int id, m0, n0, b, group;
   };
   // the first tile at or after `id` in this workgroup's sequence that has rows; id >= total: none
-  auto locate = [&](int id) {
-    const pt_gemm_args& g = gemm_args_again();
+  auto locate = [&](const pt_gemm_args& g, int id) {
     place t = {id, 0, 0, 0, 0};
     for (; t.id < total; t.id += gridDim.x) {
       const tile_coord tc = map_tile(t.id, total, tiles_m, tiles_n);
@@ -422,8 +421,7 @@ __device__ __forceinline__ void square_tile_run(int tiles_m, int tiles_n) {
   };
   __amdgpu_buffer_rsrc_t ra, rw;
   // the buffers of a tile's operand rows; empty for no tile (the last loads of a workgroup then read nothing)
-  auto open = [&](const place& t) {
-    const pt_gemm_args& g = gemm_args_again();
+  auto open = [&](const pt_gemm_args& g, const place& t) {
     int bt = t.b, k_off = 0;   // track and first element of the K slice
     if constexpr (EPI == EPI_STORE_F32) {
       if (g.k_tracks > 0) {
@@ -466,18 +464,13 @@ __device__ __forceinline__ void square_tile_run(int tiles_m, int tiles_n) {
   // wavefront's first tile for either sub-step.
   const int fr_a = (wm * TM + (lane & 15)) * BK, fr_w = BM * BK + (wn * TM + (lane & 15)) * BK;
   const int fr_ch0 = ((lane >> 4) ^ SWZ(lane & 15)) * 8, fr_ch1 = ((4 + (lane >> 4)) ^ SWZ(lane & 15)) * 8;
-  auto is_swapped = [&](const place& t) {
-    if constexpr (EPI == EPI_QKV || EPI == EPI_QKV_ROWS) {
-      const pt_gemm_args& g = gemm_args_again();
-      return t.n0 + wn * TM >= (g.H + g.Hkv) * g.hd;
-    } else {
-      return false;
-    }
+  auto is_swapped = [&](const pt_gemm_args& g, const place& t) {
+    return (EPI == EPI_QKV || EPI == EPI_QKV_ROWS) && t.n0 + wn * TM >= (g.H + g.Hkv) * g.hd;
   };
 
-  place cur = locate(blockIdx.x);
+  place cur = locate(g0, blockIdx.x);
   if (cur.id >= total) return;
-  open(cur);
+  open(g0, cur);
   static_for<LD>([&](auto I_) { issue_load(I_, 0, 0); });
   static_for<LD>([&](auto I_) { issue_load(I_, BK * 2, 1); });
   if constexpr (DEEP) {
@@ -485,7 +478,7 @@ __device__ __forceinline__ void square_tile_run(int tiles_m, int tiles_n) {
     static_for<LD>([&](auto I_) { issue_load(I_, 2 * BK * 2, 2); });
     static_for<LD>([&](auto I_) { issue_load(I_, 3 * BK * 2, 3); });
   }
-  bool swapped = is_swapped(cur);
+  bool swapped = is_swapped(g0, cur);
   int x_fr0 = (swapped ? fr_a : fr_w) + fr_ch0, y_fr0 = (swapped ? fr_w : fr_a) + fr_ch0;
   int x_fr1 = (swapped ? fr_a : fr_w) + fr_ch1, y_fr1 = (swapped ? fr_w : fr_a) + fr_ch1;
   asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((NB - 1) * LD) : "memory");
@@ -547,8 +540,9 @@ __device__ __forceinline__ void square_tile_run(int tiles_m, int tiles_n) {
         }
       }
     }
-    const place nxt = locate(cur.id + gridDim.x);
-    const bool nxt_swapped = is_swapped(nxt);
+    const pt_gemm_args& gn = gemm_args_again();
+    const place nxt = locate(gn, cur.id + gridDim.x);
+    const bool nxt_swapped = is_swapped(gn, nxt);
     PT_STAMP_TILE(cur.id, 1);
     auto next_fragments = [&] {   // from here on the first sub-step's fragments are the next tile's
       x_fr0 = (nxt_swapped ? fr_a : fr_w) + fr_ch0;
@@ -556,19 +550,19 @@ __device__ __forceinline__ void square_tile_run(int tiles_m, int tiles_n) {
     };
     if constexpr (DEEP) {
       auto step = [&](auto FIRST_, int kt) {
-        if (kt + NB == KT) { open(nxt); koff = 0; }
+        if (kt + NB == KT) { open(gemm_args_again(), nxt); koff = 0; }
         if (kt + 1 == KT) next_fragments();
         iteration(std::integral_constant<int, 0>{}, FIRST_);
       };
       step(std::true_type{}, 0);
       for (int kt = 1; kt < KT; ++kt) step(std::false_type{}, kt);
     } else {
-      if (KT == 2) { open(nxt); koff = 0; }
+      if (KT == 2) { open(gemm_args_again(), nxt); koff = 0; }
       iteration(std::integral_constant<int, 0>{}, std::true_type{});
       if (KT == 2) next_fragments();
       iteration(std::integral_constant<int, 1>{}, std::false_type{});
       for (int kt = 2; kt < KT; kt += 2) {
-        if (kt + 2 == KT) { open(nxt); koff = 0; }
+        if (kt + 2 == KT) { open(gemm_args_again(), nxt); koff = 0; }
         iteration(std::integral_constant<int, 0>{}, std::false_type{});
         if (kt + 2 == KT) next_fragments();
         iteration(std::integral_constant<int, 1>{}, std::false_type{});
