@@ -540,6 +540,39 @@ __device__ __forceinline__ void square_tile_run(int tiles_m, int tiles_n) {
         }
       }
     }
+    // ... or the row's partial sums of squares, from which the factor is formed here: requested behind the first K step and
+    // added up behind the second, so that nothing waits for them and the epilogue's registers are not asked for
+    constexpr bool SUMS = EPI == EPI_SWIGLU || EPI == EPI_QKV || (EPI == EPI_QKV_ROWS && T == 4);   // the large tile's row lookups leave no registers
+    f32x4_t sums[SUMS ? T / 4 : 1][PT_NF_MAX_SUMS / 4];
+    (void)sums;
+    auto fetch_sums = [&] {
+      if constexpr (SUMS) {
+        const pt_gemm_args& g = gemm_args_again();
+        if (g.nf_parts > 0) {
+#pragma unroll
+          for (int i = 0; i < T / 4; ++i) {
+            const float* ss = g.nf_ss + cur.b * g.nf_ss_bstride + (int64_t)min(cur.m0 + wm * TM + i * 64 + lane, g.M - 1) * g.nf_parts;
+#pragma unroll
+            for (int p = 0; p < PT_NF_MAX_SUMS / 4; ++p) sums[i][p] = *(const f32x4_t*)(ss + min(4 * p, g.nf_parts - 4));
+          }
+        }
+      }
+    };
+    auto add_sums = [&] {
+      if constexpr (SUMS) {
+        const pt_gemm_args& g = gemm_args_again();
+        if (g.nf_parts > 0) {
+#pragma unroll
+          for (int i = 0; i < T / 4; ++i) {
+            float acc_ss = 0.f;
+#pragma unroll
+            for (int p = 0; p < PT_NF_MAX_SUMS / 4; ++p)
+              if (4 * p < g.nf_parts) acc_ss = (((acc_ss + sums[i][p].x) + sums[i][p].y) + sums[i][p].z) + sums[i][p].w;
+            mine[i] = 1.0f / sqrtf(acc_ss * (1.0f / (float)g.K) + g.norm_eps);
+          }
+        }
+      }
+    };
     const pt_gemm_args& gn = gemm_args_again();
     const place nxt = locate(gn, cur.id + gridDim.x);
     const bool nxt_swapped = is_swapped(gn, nxt);
@@ -555,12 +588,17 @@ __device__ __forceinline__ void square_tile_run(int tiles_m, int tiles_n) {
         iteration(std::integral_constant<int, 0>{}, FIRST_);
       };
       step(std::true_type{}, 0);
-      for (int kt = 1; kt < KT; ++kt) step(std::false_type{}, kt);
+      fetch_sums();
+      step(std::false_type{}, 1);
+      add_sums();
+      for (int kt = 2; kt < KT; ++kt) step(std::false_type{}, kt);
     } else {
       if (KT == 2) { open(gemm_args_again(), nxt); koff = 0; }
       iteration(std::integral_constant<int, 0>{}, std::true_type{});
       if (KT == 2) next_fragments();
+      fetch_sums();
       iteration(std::integral_constant<int, 1>{}, std::false_type{});
+      add_sums();
       for (int kt = 2; kt < KT; kt += 2) {
         if (kt + 2 == KT) { open(gemm_args_again(), nxt); koff = 0; }
         iteration(std::integral_constant<int, 0>{}, std::false_type{});

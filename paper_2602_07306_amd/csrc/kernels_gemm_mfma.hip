@@ -121,11 +121,19 @@ static int choose_cfg(const pt_gemm_args& g) {
 
 bool pt_gemm_mfma_covers(const pt_gemm_args& g) { return choose_cfg(g) >= 0; }
 
+// Blocks of 32 rows inside one sequence, at positions from a multiple of 8 on.
+static bool qkv_blocks_aligned(const pt_gemm_args& g) {
+  return (g.row_map ? g.row_blocks != 0 : (g.S & 31) == 0) && (g.pos0 & 7) == 0;
+}
+
 // Configurations whose tile is at least 128 x 128 run the LDS-staged residual epilogue, which can also emit the
 // scaled bf16 copy and the per-row sums of squares; one block of sums per wavefront column range.
 int pt_gemm_mfma_fold_parts(const pt_gemm_args& g) {
-  if (g.epi != EPI_RESIDUAL) return 0;
   const int cfg = choose_cfg(g);
+  // the square tiles, except the large one's QKV form for rows of any place
+  if (g.epi == EPI_QKV || g.epi == EPI_SWIGLU)
+    return cfg == 2 || (cfg == 0 && (g.epi == EPI_SWIGLU || qkv_blocks_aligned(g))) ? (int)PT_NF_MAX_SUMS : 0;
+  if (g.epi != EPI_RESIDUAL) return 0;
   static const bool staged[GM_NCFG] = {true, true, true, false, true, false, false, false, true, true, true, true};
   if (cfg < 0 || !staged[cfg] || g.N % kWaveN[cfg]) return 0;
   return g.N / kWaveN[cfg];
@@ -171,7 +179,7 @@ int pt_launch_gemm_mfma_split(const pt_gemm_args& g, int slices, hipStream_t s) 
 // The tile kernels with an LDS-staged QKV epilogue assume 32-row blocks inside one sequence at positions from a multiple
 // of 8 on; any other rows run the form that looks up every row's place.
 static int launch_qkv(const pt_gemm_args& g, hipStream_t s, int cfg) {
-  if ((g.row_map ? g.row_blocks != 0 : (g.S & 31) == 0) && (g.pos0 & 7) == 0) return launch_epi<EPI_QKV>(g, s, cfg);
+  if (qkv_blocks_aligned(g)) return launch_epi<EPI_QKV>(g, s, cfg);
   switch (cfg) {
     case 0: return pt_gemm_mfma_launch_one<EPI_QKV_ROWS, 0>(g, s);
     case 1: return pt_gemm_mfma_launch_one<EPI_QKV_ROWS, 1>(g, s);
@@ -191,6 +199,8 @@ int pt_launch_gemm_mfma(const pt_gemm_args& g, hipStream_t s) {
   if (cfg < 0) return 0;
   if (g.nf_out && g.nf_parts != pt_gemm_mfma_fold_parts(g))
     return pt_set_error(PT_ERR_INVALID_ARGUMENT, "folded RMSNorm asked of a GEMM configuration that cannot emit it");
+  if (!g.nf_out && g.nf_parts > 0 && (g.nf_parts > pt_gemm_mfma_fold_parts(g) || (g.nf_parts & 3) || (g.nf_ss_bstride & 3) || ((uintptr_t)g.nf_ss & 15)))
+    return pt_set_error(PT_ERR_INVALID_ARGUMENT, "row sums handed to a GEMM configuration that cannot add them up");
   switch (g.epi) {
     case EPI_STORE_F32: return launch_epi<EPI_STORE_F32>(g, s, cfg);
     case EPI_RESIDUAL: return launch_epi<EPI_RESIDUAL>(g, s, cfg);

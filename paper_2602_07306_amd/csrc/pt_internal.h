@@ -201,7 +201,8 @@ struct pt_gemm_args {
   //   and, per row, the sum of out^2 over each block of N / nf_parts columns to nf_ss[b][m][part];
   //   pt_launch_row_inv_rms turns the partial sums into one factor 1 / sqrt(mean(out^2) + eps) per row;
   //   consumer, EPI_QKV / EPI_SWIGLU: the accumulators of row m are multiplied by rs_inv[b][m] before the
-  //   epilogue (A then holds bf16(h * gain), unnormalised).
+  //   epilogue (A then holds bf16(h * gain), unnormalised), or, with nf_parts > 0 (see pt_gemm_mfma_fold_parts), by the
+  //   factor that the kernel forms from the row's nf_parts sums at nf_ss [b][m] (K elements a row, norm_eps).
   void* nf_out;
   const float* nf_gain;
   float* nf_ss;
@@ -230,6 +231,7 @@ struct pt_gemm_args {
   int32_t k_tracks;
 };
 
+enum { PT_NF_MAX_SUMS = 16 };                   // sums of squares per row that a square tile adds up itself
 enum { PT_SK_PART_FLOATS = 16 << 20 };   // K-slice scratch inside the caller's workspace arena
 enum { PT_MAX_SPLITS = 32 };                   // decode-attention splits per (track, sequence, head)
 enum { PT_STATIC_SCRATCH_BYTES = 32 << 20 };   // the static device array behind pt_decode_step_static
@@ -241,7 +243,9 @@ int pt_launch_gemm_generic(const pt_gemm_args& g, hipStream_t s);
 // MFMA tile kernels: returns 1 when launched.
 int pt_launch_gemm_mfma(const pt_gemm_args& g, hipStream_t s);
 // For a residual GEMM that the MFMA tile kernels would run with an LDS-staged epilogue: the number of column
-// blocks per row whose sums of squares the kernel can emit (nf_parts), else 0.  Shape fields only.
+// blocks per row whose sums of squares the kernel can emit (nf_parts), else 0.  For a QKV or SwiGLU GEMM: the most such
+// sums per row that the kernel it would run on can turn into the row's factor itself (a multiple of 4 of them), else 0.
+// Shape fields only.
 int pt_gemm_mfma_fold_parts(const pt_gemm_args& g);
 // K slices with which the MFMA tile kernels would run this residual GEMM when the caller adds the slices (1: no split);
 // pt_launch_gemm_mfma_split leaves them in g.sk_part, [slice][batch][M][N] fp32, as the weight-streaming kernel does.

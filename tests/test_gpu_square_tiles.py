@@ -19,6 +19,8 @@ pytestmark = pytest.mark.gpu
     (3, 96, 384, 4, 4, 128, 256),       # 32-row blocks, K of six steps
     (2, 1056, 128, 2, 2, 64, 4096),     # more tiles than workgroups, the last tile of rows a quarter full
     (1, 2111, 256, 2, 1, 128, 2048),    # the same with odd positions and one KV head
+    (2, 160, 512, 8, 8, 64, 640),       # four and eight sums of squares per row, added up by the next GEMM
+    (1, 330, 1024, 16, 16, 64, 384),    # eight and sixteen, odd positions
 ])
 def test_square_tiles(tile, B, S, d_model, heads, kv_heads, hd, d_ffn):
     from paper_2602_07306_amd import binding as PB
