@@ -42,6 +42,24 @@ __device__ __forceinline__ void lds_write8(uint32_t addr, uint2 v) {
   asm volatile("ds_write_b64 %0, %1" ::"v"(addr), "v"(v) : "memory");
 }
 
+// 16 bytes from the accumulators, likewise.
+__device__ __forceinline__ void lds_write_acc(uint32_t addr, const f32x4_t& v) {
+  asm volatile("ds_write_b128 %0, %1" ::"v"(addr), "a"(v) : "memory");
+}
+
+// Sum over the N consecutive lanes (8 or 16 of an aligned group) in each of them.
+template <int N>
+__device__ __forceinline__ float lanes_sum(float x) {
+  auto moved = [](float v, auto CTRL) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), decltype(CTRL)::value, 0xf, 0xf, false));
+  };
+  x += moved(x, std::integral_constant<int, 0xb1>{});    // quad_perm 1,0,3,2
+  x += moved(x, std::integral_constant<int, 0x4e>{});    // quad_perm 2,3,0,1
+  x += moved(x, std::integral_constant<int, 0x141>{});   // row_half_mirror
+  if constexpr (N == 16) x += moved(x, std::integral_constant<int, 0x140>{});   // row_mirror
+  return x;
+}
+
 // The kernel's arguments, loaded again wherever a phase of a tile begins: kept in registers from the start, their 80
 // scalar registers and the K loop's own do not fit, and the compiler spills them around the loop.
 typedef const __attribute__((address_space(4))) pt_gemm_args* gemm_kernarg_t;
@@ -58,7 +76,7 @@ template <int BM, int NB>
 struct square_tile {
   static constexpr int BK = 64, T = BM / 32, TM = BM / 2;
   static constexpr int STG = 2 * BM * BK;                       // elements of one K step of both operands
-  static constexpr int PATCH = 16 * TM * 2 + TM * 4;            // bytes per wavefront: 16 rows of bf16, and row factors
+  static constexpr int PATCH = 16 * TM * 2 + TM * 4;            // bytes per wavefront: 16 rows of bf16 (or half rows of fp32), and row factors
   static constexpr int LDS = NB * STG * 2 + 4 * PATCH;          // 146 KB (256) or 73 KB (128: two workgroups per unit)
   static constexpr int PER_CU = BM == 256 || NB > 2 ? 1 : 2;
 };
@@ -102,56 +120,83 @@ __device__ __forceinline__ void square_tile_epilogue(const pt_gemm_args& g, cons
   (void)take8; (void)put4; (void)factors; (void)patch_lds;
 
   if constexpr (EPI == EPI_STORE_F32 || EPI == EPI_RESIDUAL) {
-    // straight from the accumulators: 16 bytes per lane, 64 bytes of 16 rows per instruction
+    // 16 rows of G tiles at a time go through the patch, as fp32, so that consecutive lanes store consecutive pieces of a
+    // row.  Straight from the accumulators consecutive lanes lie a row apart, and the memory pipe takes them 16 bytes at a
+    // time: 29 clocks a row of a 128-column tile where this form waits for nothing.  us a launch, straight / now: four K
+    // slices of 256, 4 tracks x 128 rows x 1024 9.2 / 8.2; residual with folded norm, K = 1024, 4 x 256 x 1024 15.8 / 14.2;
+    // 2048 x 1536, K = 1536 23.0 / 21.6.
+    constexpr int G = T / 2, RPF = 16 / G, NG = 2 * T;   // rows per instruction; groups in the wavefront's tile
+    static_assert(64 / CH == RPF, "a patch row is CH chunks of 16 bytes here too");
     float* out = g.out + b * g.out_bstride;
     const float* res = EPI == EPI_RESIDUAL ? g.res + b * g.res_bstride : nullptr;
-    const int m_l = wave_m + lr, n_l = wave_n + 4 * q;
+    const int m_l = wave_m + rd_row, n_l = wave_n + 4 * rd_ch;
     const int64_t off = (int64_t)m_l * g.ldo + n_l;
+    auto park = [&](auto I_) {       // group I: tiles G * (I % 2) .. of rows 16 * (I / 2) ..
+      static_for<G>([&](auto X_) {
+        constexpr int x = decltype(X_)::value;
+        lds_write_acc(patch_lds + (lr * CH + ((4 * x + q) ^ swz(lr))) * 16, acc[G * (decltype(I_)::value % 2) + x][decltype(I_)::value / 2]);
+      });
+    };
     auto run = [&](auto FULL_, auto FOLD_) {
       constexpr bool FULL = decltype(FULL_)::value, FOLD = decltype(FOLD_)::value;
-      constexpr int DEPTH = 2;                     // blocks of 16 rows whose residual values are in flight
-      f32x4_t r[DEPTH + 1][T];
-      (void)r;
-      auto load_res = [&](auto Y_) {
-        constexpr int y = decltype(Y_)::value;
-        static_for<T>([&](auto X_) {
-          constexpr int x = decltype(X_)::value;
+      constexpr int DEPTH = T == 8 ? 3 : 4;        // groups whose residual values are in flight
+      f32x4_t r[DEPTH + 1][G], val[G], gain[2];
+      float ss[G];
+      (void)r; (void)gain; (void)ss;
+      auto load_res = [&](auto I_) {
+        constexpr int i = decltype(I_)::value;
+        static_for<G>([&](auto IT_) {
+          constexpr int row = 16 * (i / 2) + RPF * decltype(IT_)::value, col = 16 * G * (i % 2);
           // past the edge: some value of the matrix, which is not used
-          const int64_t at = FULL ? off + (int64_t)(16 * y) * g.ldo + 16 * x : (int64_t)min(m_l + 16 * y, g.M - 1) * g.ldo + min(n_l + 16 * x, g.N - 4);
-          r[y % (DEPTH + 1)][x] = *(const f32x4_t*)(res + at);
+          const int64_t at = FULL ? off + (int64_t)row * g.ldo + col : (int64_t)min(m_l + row, g.M - 1) * g.ldo + min(n_l + col, g.N - 4);
+          r[i % (DEPTH + 1)][decltype(IT_)::value] = *(const f32x4_t*)(res + at);
         });
       };
-      if constexpr (EPI == EPI_RESIDUAL) {
-        static_for<DEPTH>([&](auto Y_) { load_res(Y_); });
-      }
-      static_for<T>([&](auto Y_) {
-        constexpr int y = decltype(Y_)::value;
-        if constexpr (EPI == EPI_RESIDUAL && y + DEPTH < T) load_res(std::integral_constant<int, y + DEPTH>{});
-        float ss = 0.f;
-        int n_y = n_l;   // opaque per block: the bounds tests of all blocks together would fill the scalar registers
+      auto fetch = [&] {
+        in_order();
+        static_for<G>([&](auto IT_) {
+          const int row = decltype(IT_)::value * RPF + rd_row;
+          val[decltype(IT_)::value] = *(const f32x4_t*)(patch + (row * CH + (rd_ch ^ swz(row))) * 8);
+        });
+        in_order();
+      };
+      if constexpr (EPI == EPI_RESIDUAL) static_for<DEPTH>([&](auto I_) { load_res(I_); });
+      if constexpr (FOLD)
+        for (int k = 0; k < 2; ++k) gain[k] = *(const f32x4_t*)(factors + 16 * G * k + 4 * rd_ch);
+      park(std::integral_constant<int, 0>{});
+      fetch();
+      static_for<NG>([&](auto I_) {
+        constexpr int i = decltype(I_)::value, y = i / 2, col = 16 * G * (i % 2);
+        if constexpr (EPI == EPI_RESIDUAL && i + DEPTH < NG) load_res(std::integral_constant<int, i + DEPTH>{});
+        if constexpr (i + 1 < NG) park(std::integral_constant<int, i + 1>{});
+        int n_y = n_l;   // opaque per group: the bounds tests of all groups together would fill the scalar registers
         if constexpr (!FULL) asm volatile("" : "+v"(n_y));
-        static_for<T>([&](auto X_) {
-          constexpr int x = decltype(X_)::value;
-          f32x4_t v = {acc_elem4(acc[x][y], 0), acc_elem4(acc[x][y], 1), acc_elem4(acc[x][y], 2), acc_elem4(acc[x][y], 3)};
-          if constexpr (EPI == EPI_RESIDUAL) v += r[y % (DEPTH + 1)][x];
-          if (FULL || (m_l + 16 * y < g.M && n_y + 16 * x < g.N)) *(f32x4_t*)(out + off + (int64_t)(16 * y) * g.ldo + 16 * x) = v;
+        static_for<G>([&](auto IT_) {
+          constexpr int it = decltype(IT_)::value, row = 16 * y + RPF * it;
+          f32x4_t v = val[it];
+          if constexpr (EPI == EPI_RESIDUAL) v += r[i % (DEPTH + 1)][it];
+          const bool in = FULL || (m_l + row < g.M && n_y + col < g.N);
+          if (in) *(f32x4_t*)(out + off + (int64_t)row * g.ldo + col) = v;
           if constexpr (FOLD) {   // folded RMSNorm, producer side: bf16(h * gain) and the row's sum of squares
-            const f32x4_t gain = *(const f32x4_t*)(factors + 16 * x + 4 * q);
-            ss += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
-            put4(x * 2 + (q >> 1), v.x * gain.x, v.y * gain.y, v.z * gain.z, v.w * gain.w);
+            const float sq = v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
+            ss[it] = i % 2 ? ss[it] + sq : sq;
+            const f32x4_t& gn = gain[i % 2];
+            uint2 pk;
+            pk.x = pack_bf16x2(v.x * gn.x, v.y * gn.y);
+            pk.y = pack_bf16x2(v.z * gn.z, v.w * gn.w);
+            if (in) *(uint2*)((bf16_t*)g.nf_out + b * g.nf_out_bstride + (int64_t)(m_l + row) * g.N + n_l + col) = pk;
           }
         });
-        if constexpr (FOLD) {
-          in_order();
-          bf16_t* nf = (bf16_t*)g.nf_out + b * g.nf_out_bstride + (int64_t)(wave_m + 16 * y + rd_row) * g.N + wave_n + rd_ch * 8;
-          static_for<16 / RPI>([&](auto IT_) {
+        if constexpr (i + 1 < NG) fetch();
+        if constexpr (FOLD && i % 2) {
+          float sum = 0.f;   // lane c of a row's CH lanes takes the c-th of the G sums
+          static_for<G>([&](auto IT_) {
             constexpr int it = decltype(IT_)::value;
-            if (FULL || wave_m + 16 * y + it * RPI + rd_row < g.M) *(u32x4_t*)(nf + (int64_t)(it * RPI) * g.N) = take8(it);
+            const float t = lanes_sum<CH>(ss[it]);
+            sum = rd_ch == it ? t : sum;
           });
-          in_order();
-          ss += __shfl_xor(ss, 16, 64);
-          ss += __shfl_xor(ss, 32, 64);
-          if (q == 0 && (FULL || m_l + 16 * y < g.M)) g.nf_ss[b * g.nf_ss_bstride + (int64_t)(m_l + 16 * y) * g.nf_parts + wave_n / TM] = ss;
+          const int m = m_l + 16 * y + RPF * rd_ch;
+          if (rd_ch < G && (FULL || m < g.M)) g.nf_ss[b * g.nf_ss_bstride + (int64_t)m * g.nf_parts + wave_n / TM] = sum;
         }
       });
       if constexpr (!FULL) settle();

@@ -43,3 +43,26 @@ def test_square_tiles(tile, B, S, d_model, heads, kv_heads, hd, d_ffn):
     assert_close(lg.cpu().numpy().reshape(B, S, -1), ref["logits"], BF16_TOL, "logits")
     assert_close(hid.cpu().numpy(), ref["hidden"], BF16_TOL, "hidden")
     model.close()
+
+
+@pytest.mark.parametrize("tile", [0, 2])
+@pytest.mark.parametrize("S,vocab", [(66, 136), (193, 392), (257, 264)])   # eight columns in the last tile, rows to match
+def test_square_tiles_store_ragged_edges(tile, S, vocab):
+    """fp32 results whose last tile is cut in rows and in columns (the head), and nothing behind the last column or row."""
+    from paper_2602_07306_amd import binding as PB
+    cfg = small_bf16_config(n_layers=1, block_depth=1, d_model=256, n_heads=4, n_kv_heads=4, head_dim=64, d_ffn=256, vocab=vocab, max_batch=1, max_seq=S)
+    W = I.make_weights(cfg, 44)
+    tokens = I.make_tokens(44, 1, S, cfg.vocab)
+    ref, _ = oracle_prefill(cfg, W, tokens)
+    model = PB.PTModel(cfg)
+    model.pt_init_weights(44)
+    room = torch.full(((S + 2) * vocab,), 7.0, dtype=torch.float32, device="cuda")
+    PB.pt_set_tuning(PB.PT_TUNE_GEMM_TILE_CONFIG, tile)
+    try:
+        lg, _ = model.pt_prefill(torch.from_numpy(tokens).cuda(), logits_mode=PB.PT_LOGITS_ALL, logits_out=room[vocab:-vocab].view(S, vocab))
+        torch.cuda.synchronize()
+    finally:
+        PB.pt_set_tuning(PB.PT_TUNE_GEMM_TILE_CONFIG, -1)
+    assert_close(lg.cpu().numpy().reshape(1, S, -1), ref["logits"], BF16_TOL, "logits")
+    assert bool((room[:vocab] == 7.0).all()) and bool((room[-vocab:] == 7.0).all())
+    model.close()
