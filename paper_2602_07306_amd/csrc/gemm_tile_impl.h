@@ -653,8 +653,11 @@ __device__ __forceinline__ void square_tile_run(int tiles_m, int tiles_n) {
     }
     x_fr1 = (nxt_swapped ? fr_a : fr_w) + fr_ch1;
     y_fr1 = (nxt_swapped ? fr_w : fr_a) + fr_ch1;
-    // the compiler does not see the MFMAs inside the assembly: their results take up to 18 cycles to arrive
+    // The compiler does not see the MFMAs inside the assembly: their results take up to 18 cycles to arrive.  Every
+    // accumulator passes through a statement behind the wait, so that nothing can read one in front of it.
     asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+#pragma unroll
+    for (int i = 0; i < T * T; ++i) asm volatile("" : "+a"(acc[i / T][i % T]));
     PT_STAMP_TILE(cur.id, 2);
     PT_STAMP_TILE(cur.id, 3);
     square_tile_epilogue<T, EPI>(gemm_args_again(), acc, (bf16_t*)(smem + NB * STG * 2 + wave * S::PATCH), cur.b, cur.m0 + wm * TM, cur.n0 + wn * TM,
