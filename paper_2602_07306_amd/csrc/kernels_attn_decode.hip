@@ -470,12 +470,15 @@ __global__ void __launch_bounds__(64, HD == 64 ? 3 : 2) attn_decode_wave_kernel(
   for (int i = 0; i < VP; ++i) v_off[i] = vr * (uint32_t)(a.s_pad * 2) + (((lane % VCH) ^ vswz(i * VRPI + vr)) * 16);
   char* kt = smem;
   char* vt = smem + TK * KROW;
+  // LDS byte addresses: a cast of the generic pointer at every load is a 64-bit sum and a test for null that are kept in
+  // scalar registers from tile to tile, 40 of them spilled into vector lanes and back around each tile's loads
+  const uint32_t kt_lds = (uint32_t)(uintptr_t)(lptr_t)smem, vt_lds = kt_lds + TK * KROW;
   int v_step = VRPI * a.s_pad * 2;
   auto load_k = [&](int kb) {
     int at = kb * KROW;
 #pragma unroll
     for (int i = 0; i < NK; ++i) {
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rk, (lptr_t)(kt + i * 1024), 16, k_off[i % KP], at, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rk, (lptr_t)(uintptr_t)(kt_lds + i * 1024), 16, k_off[i % KP], at, 0, 0);
       at += KRPI * KROW;
     }
   };
@@ -484,7 +487,7 @@ __global__ void __launch_bounds__(64, HD == 64 ? 3 : 2) attn_decode_wave_kernel(
     int at = kb * 2;
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rv, (lptr_t)(vt + i * 1024), 16, v_off[i % VP], at, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rv, (lptr_t)(uintptr_t)(vt_lds + i * 1024), 16, v_off[i % VP], at, 0, 0);
       at += v_step;
     }
   };

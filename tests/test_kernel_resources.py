@@ -56,6 +56,16 @@ def test_gemm_tiles_spill_no_scalar_registers(fragment):
     assert seen > 0
 
 
+def test_decode_attention_spills_no_scalar_registers():
+    seen = 0
+    for src in HOT["attn_decode"]:
+        for name, res in load(src).items():
+            if "attn_decode" in name:
+                seen += 1
+                assert res["SGPRs Spill"] == 0, (src, name, res)
+    assert seen >= 7   # the wavefront and the workgroup form and the vector kernel at both head widths, and the combine
+
+
 def test_the_big_gemm_tile_keeps_its_accumulators_in_accumulation_registers():
     """256 x 256 tile, four wavefronts: 256 accumulators per lane, which only fit beside the staging registers when
     they live in AGPRs."""
