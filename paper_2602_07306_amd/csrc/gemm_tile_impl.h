@@ -169,13 +169,13 @@ __device__ __forceinline__ void square_tile_epilogue(const pt_gemm_args& g, cons
         constexpr int i = decltype(I_)::value, y = i / 2, col = 16 * G * (i % 2);
         if constexpr (EPI == EPI_RESIDUAL && i + DEPTH < NG) load_res(std::integral_constant<int, i + DEPTH>{});
         if constexpr (i + 1 < NG) park(std::integral_constant<int, i + 1>{});
-        int n_y = n_l;   // opaque per group: the bounds tests of all groups together would fill the scalar registers
-        if constexpr (!FULL) asm volatile("" : "+v"(n_y));
+        int m_i = m_l, n_i = n_l;   // opaque per group: the bounds tests of all groups together would fill the scalar registers
+        if constexpr (!FULL) asm volatile("" : "+v"(m_i), "+v"(n_i));
         static_for<G>([&](auto IT_) {
           constexpr int it = decltype(IT_)::value, row = 16 * y + RPF * it;
           f32x4_t v = val[it];
           if constexpr (EPI == EPI_RESIDUAL) v += r[i % (DEPTH + 1)][it];
-          const bool in = FULL || (m_l + row < g.M && n_y + col < g.N);
+          const bool in = FULL || (m_i + row < g.M && n_i + col < g.N);
           if (in) *(f32x4_t*)(out + off + (int64_t)row * g.ldo + col) = v;
           if constexpr (FOLD) {   // folded RMSNorm, producer side: bf16(h * gain) and the row's sum of squares
             const float sq = v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;

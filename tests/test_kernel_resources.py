@@ -9,12 +9,15 @@ import pytest
 
 from paper_2602_07306_amd import build as B
 
+TILE_SOURCES = ["kernels_gemm_mfma_store.hip", "kernels_gemm_mfma_residual.hip", "kernels_gemm_mfma_swiglu.hip",
+                "kernels_gemm_mfma_qkv_a.hip", "kernels_gemm_mfma_qkv_b.hip", "kernels_gemm_mfma_qkv_c.hip",
+                "kernels_gemm_mfma_qkv_d.hip", "kernels_gemm_mfma_qkv_rows_a.hip",
+                "kernels_gemm_mfma_qkv_rows_b.hip", "kernels_gemm_mfma_qkv_rows_c.hip"]
+
 # kernel name fragment -> sources that instantiate it
 HOT = {
-    "gemm_mfma_kernel": ["kernels_gemm_mfma_store.hip", "kernels_gemm_mfma_residual.hip", "kernels_gemm_mfma_swiglu.hip",
-                         "kernels_gemm_mfma_qkv_a.hip", "kernels_gemm_mfma_qkv_b.hip", "kernels_gemm_mfma_qkv_c.hip",
-                         "kernels_gemm_mfma_qkv_d.hip", "kernels_gemm_mfma_qkv_rows_a.hip",
-                         "kernels_gemm_mfma_qkv_rows_b.hip", "kernels_gemm_mfma_qkv_rows_c.hip"],
+    "gemm_mfma_kernel": TILE_SOURCES,
+    "gemm_tile_deep_kernel": TILE_SOURCES,
     "gemm_dl_kernel": ["kernels_gemm_mfma_store.hip", "kernels_gemm_mfma_residual.hip", "kernels_gemm_mfma_swiglu.hip",
                        "kernels_gemm_mfma_qkv_a.hip", "kernels_gemm_mfma_qkv_rows_a.hip"],
     "gemm_skinny_kernel": ["kernels_gemm_skinny.hip"],
@@ -43,7 +46,7 @@ def test_hot_kernels_use_no_scratch_memory(fragment):
     assert seen > 0, "no kernel named *%s* in %s" % (fragment, HOT[fragment])
 
 
-@pytest.mark.parametrize("fragment", ["gemm_mfma_kernel", "gemm_dl_kernel"])
+@pytest.mark.parametrize("fragment", ["gemm_mfma_kernel", "gemm_tile_deep_kernel", "gemm_dl_kernel"])
 def test_gemm_tiles_spill_no_scalar_registers(fragment):
     """Scalar registers spill into lanes of vector registers, which the scratch test does not see.  The QKV form for rows
     of any place (the last template argument, the epilogue, is 4) is left out: it spills a few around its row table."""
@@ -66,9 +69,15 @@ def test_decode_attention_spills_no_scalar_registers():
     assert seen >= 7   # the wavefront and the workgroup form and the vector kernel at both head widths, and the combine
 
 
-def test_the_big_gemm_tile_keeps_its_accumulators_in_accumulation_registers():
-    """256 x 256 tile, four wavefronts: 256 accumulators per lane, which only fit beside the staging registers when
-    they live in AGPRs."""
-    res = load("kernels_gemm_mfma_swiglu.hip")
-    big = [r for n, r in res.items() if "gemm_mfma_kernelILi256ELi256ELi2ELi2ELi64" in n]
-    assert big and all(r["AGPRs"] == 256 for r in big), big
+def test_the_square_gemm_tiles_keep_their_accumulators_in_accumulation_registers():
+    """256 x 256 and 128 x 128 tiles of four wavefronts: 256 and 64 accumulators per lane.  The large ones only fit beside
+    the MFMA operands, addresses and residual rows when they live in AGPRs, and the inline assembly of both ties them there."""
+    big, small = {}, {}
+    for src in TILE_SOURCES:
+        for name, res in load(src).items():
+            if "gemm_mfma_kernelILi256ELi256ELi2ELi2ELi64" in name:
+                big[name] = res["AGPRs"]
+            elif "gemm_mfma_kernelILi128ELi128ELi2ELi2ELi64" in name or "gemm_tile_deep_kernelILi128" in name:
+                small[name] = res["AGPRs"]
+    assert len(big) == 5 and all(n == 256 for n in big.values()), big      # one per epilogue
+    assert len(small) == 10 and all(n >= 64 for n in small.values()), small   # two and four K steps in flight
