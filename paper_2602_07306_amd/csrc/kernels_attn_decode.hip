@@ -418,11 +418,8 @@ __global__ void __launch_bounds__(256, HD == 64 ? 3 : 2) attn_decode_tiled_kerne
 // whole cache lines: K [64 x HD], V^T [HD x 64 keys]; a cache row holds a multiple of 64 positions, so a tile never leaves
 // it.  MFMA layout, softmax state and partials as above.
 // What bounds it is HBM again, and past a thousand wavefronts their many streams get slower than the larger tiles above
-// (4 tracks x 32 sequences x 16 heads x 2048 keys 201 us against 197; tiles of 128 keys here 209).  us a launch with the
-// kernel above / with this one, hd = 128 (8 tracks, 2 or 4 KV heads): 64 heads x 2048 keys 34.3 / 27.4, 128 x 512 21.8 / 19.4,
-// 256 x 2048 67.7 / 60.2, 512 x 128 21.4 / 17.2, 512 x 512 47.7 / 34.2, 768 x 512 64.9 / 46.1, 1024 x 512 67.0 / 60.3,
-// 1024 x 4096 355 / 356, 2048 x 512 120 / 121; hd = 64 (4 tracks, 16 heads): 512 x 256 14.7 / 15.7, 512 x 512 26.1 / 22.5,
-// 1024 x 256 23.8 / 22.4, 1024 x 1024 60.0 / 56.4, 1024 x 4096 203 / 192, 1536 x 512 48.1 / 47.1, 4096 x 1024 207 / 217.
+// (4 tracks x 32 sequences x 16 heads x 2048 keys 201 us against 197; tiles of 128 keys here 209).  Where it runs, and both
+// sides' times: pt_decode_wave_ranges.
 template <int HD>
 __global__ void __launch_bounds__(64, HD == 64 ? 3 : 2) attn_decode_wave_kernel(const pt_attn_args a, int nsplit, int keys_per_split) {
 #if defined(__HIP_DEVICE_COMPILE__)   // the buffer types exist on the device only
@@ -654,10 +651,8 @@ int pt_launch_attn_decode(const pt_attn_args& a, hipStream_t s) {
     // 32-bit offsets inside a head's cache; whole tiles of 64 positions
     const bool wave_fits = a.kv_head_elems * 2 < ((int64_t)1 << 31) && (int64_t)a.hd * a.s_pad * 2 < ((int64_t)1 << 31) &&
                            a.kv_head_elems % (64 * a.hd) == 0;
-    if (wave_fits && gbase <= 1024 && (a.hd == 128 ? gbase >= 64 : gbase >= 512 && (nkeys >= 384 || gbase == 1024))) {
-      // two wavefronts per compute unit are enough; fewer heads are split into ranges of at least 256 keys
-      int ns = a.hd == 128 ? (int)std::max<int64_t>(1, std::min<int64_t>(512 / gbase, (nkeys + 255) / 256)) : 1;
-      ns = std::min(ns, a.max_splits);
+    int ns = wave_fits ? std::min(pt_decode_wave_ranges(a.hd, gbase, nkeys), a.max_splits) : 0;
+    if (ns > 0) {
       const int kps = ((nkeys + ns - 1) / ns + 63) / 64 * 64;
       ns = (nkeys + kps - 1) / kps;          // no empty range
       const dim3 grid((unsigned)ns, (unsigned)a.Hkv, (unsigned)z);

@@ -303,6 +303,27 @@ int pt_launch_attn_generic(const pt_attn_args& a, hipStream_t s);
 int pt_launch_attn_prefill_mfma(const pt_attn_args& a, hipStream_t s);  // 1: LDS-tiled, 2: with a masked last tile
 int pt_launch_attn_decode(const pt_attn_args& a, hipStream_t s);        // 1: matrix-core kernel, 2: vector kernel
 
+// Decode attention on the matrix cores: the number of key ranges per head of the cache (`heads`: tracks x sequences x KV
+// heads) if a wavefront takes each (attn_decode_wave_kernel), or 0 if a workgroup does (attn_decode_tiled_kernel).
+// us a launch inside the models, combine included, workgroup / wavefront form:
+//  hd = 128 (Large): 64 heads x 128 keys 13.0 / 9.9, 320 16.6 / 13.5, 1024 23.2 / 20.5; 192 x 512 20.4 / 19.8, 256 x 320 18.3 /
+//    16.0, 512 x 512 33.2 / 31.3, 1024 x 1024 108 / 107; 1024 x 4096 355 / 356, 2048 x 512 120 / 121.
+//    Two wavefronts per compute unit are enough.  With fewer heads, ranges of at least 256 keys share the units, but the
+//    combine is a launch of 3 to 4 us: it pays from about six keys per head on (one range / two: 64 x 320 13.5 / 14.7, 64 x 512
+//    17.4 / 16.8; 128 x 512 17.8 / 18.7, 128 x 768 22.7 / 21.7; 192 x 512 19.8 / 22.1, 192 x 2048 51.1 / 46.5; 256 x 1024 32.1 / 34.8).
+//  hd = 64 (Mid): the workgroup form splits the keys past 512, which is its combine; up to there it is as fast with two
+//    workgroups per compute unit (512 x 256 13.4 / 13.8, 512 x 512 19.6 / 20.4, 512 x 640 26.8 / 23.0) and no longer with more (576 x 256
+//    15.4 / 14.5, 576 x 512 23.0 / 21.0, 768 x 512 26.1 / 24.6, 960 x 320 22.9 / 21.0, 1024 x 1024 57.8 / 52.8).  Past a thousand
+//    heads their many streams are slower (2048 x 2048 197 / 201).
+static inline int pt_decode_wave_ranges(int hd, int64_t heads, int nkeys) {
+  if (heads > 1024) return 0;
+  if (hd == 64) return heads >= (nkeys > 512 ? 512 : 576) ? 1 : 0;
+  if (hd != 128 || heads < 64) return 0;
+  if (nkeys < 6 * heads) return 1;
+  const int fill = (int)(512 / heads), by_len = (nkeys + 255) / 256;
+  return fill < 1 ? 1 : fill < by_len ? fill : by_len;
+}
+
 // Tuning overrides (pt_set_tuning): tile configuration of the MFMA GEMM (-1 = by shape) and plan of the
 // weight-streaming GEMM (0 = by shape).
 extern int pt_tune_gemm_cfg;

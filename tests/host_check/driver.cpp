@@ -10,6 +10,7 @@
 #include <vector>
 
 #include "pt.h"
+#include "pt_internal.h"
 #include "host_check.h"
 
 #ifndef HC_SHRINK
@@ -85,6 +86,24 @@ static void invalid_configs() {
   EXPECT(pt_destroy(nullptr) == PT_ERR_NULL_POINTER);
   EXPECT(pt_seq_len(nullptr) < 0 && pt_merge_count(nullptr) < 0);
   EXPECT(pt_set_tuning(99, 0) == PT_ERR_INVALID_ARGUMENT && pt_set_tuning(PT_TUNE_FOLD_RMSNORM, 1) == PT_OK);
+}
+
+// Which form of decode attention a number of cache heads and keys runs on, and in how many key ranges.
+static void decode_forms() {
+  for (int hd : {64, 128})
+    for (int nkeys = 1; nkeys <= 4096; nkeys += nkeys < 600 ? 1 : 37) {
+      int last = 0;
+      for (int64_t heads = 1; heads <= 1200; ++heads) {
+        const int n = pt_decode_wave_ranges(hd, heads, nkeys);
+        EXPECT(n >= 0 && n <= 8);
+        // one run of head counts, no size of its own inside or beside it
+        EXPECT(heads > 1024 ? n == 0 : !last || n);
+        EXPECT(n <= 1 || (hd == 128 && n * heads <= 512 && nkeys > 256 * (n - 1) && nkeys >= 6 * heads));
+        last = n;
+      }
+    }
+  EXPECT(pt_decode_wave_ranges(64, 960, 300) == 1 && pt_decode_wave_ranges(64, 512, 512) == 0 && pt_decode_wave_ranges(64, 512, 513) == 1);
+  EXPECT(pt_decode_wave_ranges(128, 256, 320) == 1 && pt_decode_wave_ranges(128, 64, 1024) == 4 && pt_decode_wave_ranges(128, 63, 1024) == 0);
 }
 
 static void run_model(const pt_config& c, int mode) {
@@ -223,6 +242,7 @@ static void run_model(const pt_config& c, int mode) {
 
 int main() {
   invalid_configs();
+  decode_forms();
   // stateless entry points
   {
     io_alloc io;

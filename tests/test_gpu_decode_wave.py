@@ -17,7 +17,10 @@ pytestmark = pytest.mark.gpu
     (128, 8, 1, 4, 16, 64),    # groups of eight
     (128, 4, 2, 4, 8, 700),    # three ranges of 256 keys
     (128, 2, 2, 8, 32, 129),   # 512 heads, one range
-    (64, 4, 4, 4, 32, 385),    # 512 heads of 64
+    (64, 4, 4, 4, 32, 385),    # 512 heads of 64 up to 512 keys: the workgroup form
+    (64, 4, 4, 4, 32, 512),    # ... and past them
+    (64, 4, 4, 5, 32, 191),    # 640 of them, the fourth tile begins
+    (128, 4, 4, 2, 24, 320),   # 192 heads, one range: fewer than six keys a head
     (64, 16, 16, 1, 64, 30),   # 1024 of them, short
 ])
 @pytest.mark.parametrize("ragged", [False, True])
