@@ -1075,12 +1075,14 @@ static int launch_cfg(const pt_gemm_args& g, hipStream_t s) {
   if (total > 0x7fffffff) return pt_set_error(PT_ERR_INVALID_ARGUMENT, "GEMM grid too large");
   unsigned grid = (unsigned)total;
   if constexpr (SQUARE && BM == 128) {
-    // Four K steps of loads in flight, one workgroup per compute unit, instead of two with two steps each: where tiles
-    // leave no second workgroup (us inside the Mid model, two steps / four: 100 rows, QKV 20.7 / 18.6, gate/up 22.2 / 20.2,
-    // K slices of down 20.0 / 18.3; 4 tracks x 300 rows x 1024, K = 4096 33.7 / 29.1), and where one tile covers the rows, so
-    // that the weights' way from HBM is the time and K is not long enough to hide the tiles' ends (8 tracks x 96 rows x
-    // 16384: K = 2048 129 / 124, but K = 8192 176 / 195).
-    if ((total <= pt_device_cus() || (tiles_m == 1 && g.K < 4096)) && g.K >= 4 * BK) {
+    // Four K steps of loads in flight, one workgroup per compute unit, instead of two with two steps each.  Where tiles leave no
+    // second workgroup (us inside the Mid model, two steps / four: 100 rows, QKV 20.7 / 18.6, gate/up 22.2 / 20.2, K slices of
+    // down 20.0 / 18.3; 4 tracks x 300 rows x 1024, K = 4096 33.7 / 29.1).  Where one tile covers the rows, and not all of its
+    // own, also in an odd number of rounds, whose last one would leave every unit with one of its two workgroups (gate/up of 8
+    // tracks, K = 2048, 576 tiles: 66 rows 78 / 71, 96 rows 83 / 79, 112 rows 84 / 81, but 128 rows 85 / 86; 704 tiles 96 rows 90 / 86;
+    // in four rounds, 832 tiles, 96 rows 103 / 107 and 128 rows 109 / 117; three rounds at K = 1024: 66 rows 43 / 41, 96 rows 44 / 44).
+    const int64_t rounds = (total + pt_device_cus() - 1) / pt_device_cus();
+    if ((rounds == 1 || (rounds % 2 && tiles_m == 1 && g.M <= 112 && g.K < 4096)) && g.K >= 4 * BK) {
       auto deep = gemm_tile_deep_kernel<BM, 4, EPI>;
       PT_SET_MAX_LDS_ONCE(deep, (square_tile<BM, 4>::LDS));
       const unsigned resident = (unsigned)pt_device_cus();

@@ -107,9 +107,12 @@ static int choose_cfg(const pt_gemm_args& g) {
       if (cfg_fits(g, *c)) return *c;
     return -1;
   }
-  // One tile of rows and many rounds of 2: the weights' way from HBM is the time, and 4 has most of them in flight (gate/up of
-  // Large: 96 rows 109 us against 121 on 2 and 114 on 0, 128 rows 112 against 121 and 119).
-  if (g.M <= 128 && (int64_t)((g.N + 127) / 128) * g.batch >= 4 * (int64_t)pt_device_cus() && cfg_fits(g, 4)) return 4;
+  // One tile of rows and more than three rounds of 2 at one tile per compute unit: the weights' way from HBM is the time, and 4
+  // has most of them in flight while K is long (gate/up of 8 tracks, us on 4 / on 2: K = 2048, 832 tiles of 2, 96 rows 98 / 98, 128
+  // rows 100 / 104; 960 tiles 107 / 108 and 110 / 114; 1024 (Large) 112 / 112 and 115 / 119; K = 4096, 960 tiles 192 / 202 and 197 /
+  // 208.  Not at K = 1024: 960 tiles 59 / 56 and 60 / 59, 1024 tiles 62 / 57 and 62 / 60; and not in three rounds: K = 2048, 768
+  // tiles 93 / 85 and 96 / 89).
+  if (g.M <= 128 && g.K >= 2048 && (int64_t)((g.N + 127) / 128) * g.batch > 3 * (int64_t)pt_device_cus() && cfg_fits(g, 4)) return 4;
   int best = -1;
   double best_us = 1e30;
   for (int cfg : {0, 4, 2}) {

@@ -66,3 +66,31 @@ def test_square_tiles_store_ragged_edges(tile, S, vocab):
     assert_close(lg.cpu().numpy().reshape(1, S, -1), ref["logits"], BF16_TOL, "logits")
     assert bool((room[:vocab] == 7.0).all()) and bool((room[-vocab:] == 7.0).all())
     model.close()
+
+
+@pytest.mark.parametrize("S,d_model,heads,d_ffn,vocab", [
+    (66, 256, 4, 9216, 512),       # gate/up: 576 tiles, K of four steps; workgroups with two and with three of them
+    (96, 384, 96, 9216, 512),      # six steps: the four buffers turn on from tile to tile; QKV likewise, in 32-row blocks
+    (112, 640, 96, 8448, 512),     # ten steps; QKV of rows of any place, 528 tiles of gate/up
+    (70, 256, 4, 256, 73728),      # the head: 576 tiles with results in fp32
+])
+def test_four_step_tile_with_several_tiles_of_a_launch(S, d_model, heads, d_ffn, vocab):
+    """One tile of rows and an odd number of rounds of the 128 x 128 tile: the form with four K steps in flight runs from one
+    tile into the next."""
+    from paper_2602_07306_amd import binding as PB
+    cfg = small_bf16_config(n_tracks=4, n_layers=1, block_depth=1, d_model=d_model, n_heads=heads, n_kv_heads=heads, head_dim=64, d_ffn=d_ffn,
+                            vocab=vocab, max_batch=1, max_seq=S)
+    W = I.make_weights(cfg, 45)
+    tokens = I.make_tokens(45, 1, S, cfg.vocab)
+    ref, _ = oracle_prefill(cfg, W, tokens)
+    model = PB.PTModel(cfg)
+    model.pt_init_weights(45)
+    PB.pt_set_tuning(PB.PT_TUNE_GEMM_TILE_CONFIG, 2)
+    try:
+        lg, hid = model.pt_prefill(torch.from_numpy(tokens).cuda(), logits_mode=PB.PT_LOGITS_ALL, want_hidden=True)
+        torch.cuda.synchronize()
+    finally:
+        PB.pt_set_tuning(PB.PT_TUNE_GEMM_TILE_CONFIG, -1)
+    assert_close(lg.cpu().numpy().reshape(1, S, -1), ref["logits"], BF16_TOL, "logits")
+    assert_close(hid.cpu().numpy(), ref["hidden"], BF16_TOL, "hidden")
+    model.close()
