@@ -144,10 +144,15 @@ int pt_gemm_mfma_fold_parts(const pt_gemm_args& g) {
 
 // Residual GEMMs whose tiles leave compute units idle: every K slice is a launch's worth of tiles more, and the kernel
 // that normalises adds the slices to the residual stream (it would run anyway).  The slices cost their traffic, taken at
-// 4 TB/s.  Measured, out + down projection in us without / with slices: Mid (4 tracks, width 1024) 128 rows 17.7 + 44.5
-// / 12.0 + 18.3, 256 rows 17.9 + 44.3 / 18.3 + 20.0; Large (8 x 2048) 96 rows 31.6 + 84.4 / 23.0 + 59.4; one-GPU share
-// (1 x 8192) 128 rows 80.9 + 283 / 41.7 + 102; the normalising kernel takes 1 to 9 us more.
-// What bounds a slice is the latency of its few K steps' weights on their way from HBM, hence estimates of their own.
+// 4 TB/s.  Inside the models, out + down projection + normalising kernel in us a layer, without slices / as chosen: Mid (4 tracks,
+// width 1024) 96 rows 16.6 + 39.4 + 1.5 / 11.4 + 17.2 + 14.6, 300 rows 16.1 + 35.8 + 6.2 / 16.6 + 22.2 + 9.4; Large (8 x 2048) 96 rows
+// 29.5 + 83.7 + 16.1 / 22.2 + 58.9 + 20.1; one-GPU share (1 x 8192) 128 rows 78 + 279 + 29 / 41 + 100 + 41, 384 rows 81 + 281 + 37 /
+// 82 + 208 + 46.
+// What bounds a slice is the latency of its few K steps' weights on their way from HBM, hence estimates of their own, for
+// either side.  They are fitted on 128 x 128 tiles staged through registers, which took longer; with the present ones they
+// still choose no slices that cost more than none at 65 to 700 rows of these models and of a dense one of width 8192, but too
+// few in places (Mid 256 rows, out projection not cut: a layer 99 us against 97 with four slices of both; Large 128 rows 284
+// against 280; share 384 rows 840 against 834).
 static double slice_us(const pt_gemm_args& g, int cfg, int slices) {
   const int bm = cfg == 0 ? 256 : 128, bn = cfg == 2 ? 128 : 256;
   const int64_t tiles = (int64_t)((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn) * g.batch * slices;
@@ -164,8 +169,7 @@ int pt_gemm_mfma_ksplit(const pt_gemm_args& g) {
   if (cfg < 0 || g.epi != EPI_RESIDUAL || g.blk_group || !g.sk_part || ((uintptr_t)g.sk_part & 15) || pt_tune_gemm_cfg >= 0) return 1;
   const double traffic_us = (double)g.batch * g.M * g.N * 8.0 / 4e6;   // a slice written and read once
   double best_us = 1e30;
-  if (g.M > 64)
-    for (int c : {0, 4, 2}) best_us = std::min(best_us, slice_us(g, c, 1));
+  for (int c : {0, 4, 2}) best_us = std::min(best_us, slice_us(g, c, 1));
   int best = 1;
   for (int slices = 2; slices <= 16; slices *= 2) {
     if (g.K % (slices * 2 * GM_BK) || (int64_t)slices * g.batch * g.M * g.N > g.sk_part_floats) break;

@@ -247,7 +247,7 @@ int pt_launch_gemm_mfma(const pt_gemm_args& g, hipStream_t s);
 // sums per row that the kernel it would run on can turn into the row's factor itself (a multiple of 4 of them), else 0.
 // Shape fields only.
 int pt_gemm_mfma_fold_parts(const pt_gemm_args& g);
-// K slices with which the MFMA tile kernels would run this residual GEMM when the caller adds the slices (1: no split);
+// K slices with which the MFMA tile kernels would run this residual GEMM of more than 64 rows when the caller adds the slices (1: no split);
 // pt_launch_gemm_mfma_split leaves them in g.sk_part, [slice][batch][M][N] fp32, as the weight-streaming kernel does.
 int pt_gemm_mfma_ksplit(const pt_gemm_args& g);
 int pt_launch_gemm_mfma_split(const pt_gemm_args& g, int slices, hipStream_t s);   // returns 1
