@@ -269,7 +269,7 @@ int main() {
   };
   for (int mode = 0; mode < 2; ++mode)
     for (const pt_config& c : models) run_model(c, mode);
-  EXPECT(hc_sliced() > 0);
+  EXPECT(hc_sliced() > 0 && hc_row_sums() > 0 && hc_rows_apart() > 0);
   printf("host_check: %ld launches (%ld sliced GEMMs above 64 rows), %ld buffers checked, all inside their memory\n",
          hc_launches(), hc_sliced(), hc_checked());
   return 0;

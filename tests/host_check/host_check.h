@@ -11,6 +11,8 @@ void hc_set_mode(int mode);     // 0: tuned kernels refuse every shape, 1: they 
 long hc_checked(void);          // buffers checked so far
 long hc_launches(void);         // launches seen so far
 long hc_sliced(void);           // of these, residual GEMMs of more than 64 rows that left K slices
+long hc_row_sums(void);         // GEMMs that were handed the sums of squares of their rows
+long hc_rows_apart(void);       // GEMMs that form a normalised operand from rows further apart than they are long
 void* hc_scratch_address(void); // the address hipGetSymbolAddress reports for the static scratch array (driver's)
 #ifdef __cplusplus
 }

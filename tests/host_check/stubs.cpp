@@ -16,7 +16,7 @@
 namespace {
 struct range { uintptr_t lo, hi; const char* name; };
 std::vector<range> g_ranges;
-long g_checked = 0, g_launches = 0, g_sliced = 0;
+long g_checked = 0, g_launches = 0, g_sliced = 0, g_row_sums = 0, g_apart = 0;
 int g_mode = 0;
 
 void need(const void* p, double bytes, const char* what) {
@@ -41,7 +41,7 @@ void check_gemm(const pt_gemm_args& g, const char* who) {
     const int bt = g.k_tracks > 0 ? b % g.k_tracks : b;                       // track and first element of a K slice
     const size_t k0 = g.k_tracks > 0 ? (size_t)(b / g.k_tracks) * g.K : 0;
     if (g.norm_src) {
-      need(g.norm_src + b * g.norm_bstride, ((double)(g.M - 1) * g.K + g.K) * 4, "GEMM norm_src");
+      need(g.norm_src + b * g.norm_bstride, ((double)(g.M - 1) * g.lda + g.K) * 4, "GEMM norm_src");
       need(g.norm_gain + b * g.norm_gbstride, g.K * 4.0, "GEMM norm_gain");
     } else if (g.a_rows) {
       // gathered rows: any row of the track's A may be read; the table itself holds M entries
@@ -59,6 +59,15 @@ void check_gemm(const pt_gemm_args& g, const char* who) {
       need(g.grp_base + b * g.grp_info_bstride, g.n_groups * 4.0, "GEMM grp_base");
     }
     if (g.rs_inv) need(g.rs_inv + b * g.rs_bstride, g.M * 4.0, "GEMM rs_inv");
+    if (!g.nf_out && g.nf_parts > 0) {
+      // the row's sums of squares, added up by the consumer: read four at a time
+      const float* ss = g.nf_ss + b * g.nf_ss_bstride;
+      if (g.rs_inv || g.nf_parts % 4 || g.nf_parts > pt_gemm_mfma_fold_parts(g) || ((uintptr_t)ss & 15) || !(g.norm_eps > 0)) {
+        fprintf(stderr, "host_check: %s cannot use the row sums that it is handed\n", who);
+        abort();
+      }
+      need(ss, (double)g.M * g.nf_parts * 4, "GEMM nf_ss of the consumer");
+    }
     if (g.epi == EPI_STORE_F32 || g.epi == EPI_RESIDUAL) {
       need(g.out + b * g.out_bstride, ((double)(g.M - 1) * g.ldo + g.N) * 4, "GEMM out");
       if (g.epi == EPI_RESIDUAL) need(g.res + b * g.res_bstride, ((double)(g.M - 1) * g.ldo + g.N) * 4, "GEMM res");
@@ -112,20 +121,35 @@ extern "C" void hc_set_mode(int mode) { g_mode = mode; }
 extern "C" long hc_checked(void) { return g_checked; }
 extern "C" long hc_launches(void) { return g_launches; }
 extern "C" long hc_sliced(void) { return g_sliced; }
+extern "C" long hc_row_sums(void) { return g_row_sums; }
+extern "C" long hc_rows_apart(void) { return g_apart; }
 
 // ------------------------------------------------------------------------------------------------ GEMM family
 // mode 0: the tuned kernels refuse everything (generic path); mode 1: they take everything they are offered,
 // fold the norm where asked and split K in residual GEMMs of up to 256 rows.
 int pt_tune_gemm_cfg = -1, pt_tune_skinny_plan = 0, pt_tune_attn_prefill = 0;
-int pt_launch_gemm_generic(const pt_gemm_args& g, hipStream_t) { check_gemm(g, "generic GEMM"); return PT_OK; }
+// fp32, a handful of rows: the form that can take norm_src, whose rows lie lda apart
+bool pt_gemm_generic_fuses_norm(const pt_gemm_args& g) {
+  return g_mode == 1 && g.dtype == PT_F32 && g.M <= 8 && !g.blk_group && !g.a_rows && g.epi != EPI_RESIDUAL && !((g.K | g.lda | g.ldb) & 3);
+}
+int pt_launch_gemm_generic(const pt_gemm_args& g, hipStream_t) {
+  if (g.norm_src && !pt_gemm_generic_fuses_norm(g)) { fprintf(stderr, "host_check: generic GEMM cannot form its operand\n"); abort(); }
+  if (g.norm_src && g.lda != g.K) ++g_apart;
+  check_gemm(g, "generic GEMM");
+  return PT_OK;
+}
 bool pt_gemm_mfma_covers(const pt_gemm_args& g) { return g_mode == 1 && g.dtype == PT_BF16 && g.K % 128 == 0; }
 int pt_launch_gemm_mfma(const pt_gemm_args& g, hipStream_t) {
   if (!pt_gemm_mfma_covers(g)) return 0;
+  if (!g.nf_out && g.nf_parts > 0) ++g_row_sums;
   check_gemm(g, "MFMA GEMM");
   return 1;
 }
+// a producer's sums per row; a consumer of QKV takes sums for 32-row blocks only, and finished factors otherwise
 int pt_gemm_mfma_fold_parts(const pt_gemm_args& g) {
-  return pt_gemm_mfma_covers(g) && g.epi == EPI_RESIDUAL && g.N % 128 == 0 ? g.N / 128 : 0;
+  if (!pt_gemm_mfma_covers(g)) return 0;
+  if (g.epi == EPI_SWIGLU || (g.epi == EPI_QKV && (g.row_map ? g.row_blocks != 0 : g.S % 32 == 0))) return PT_NF_MAX_SUMS;
+  return g.epi == EPI_RESIDUAL && g.N % 128 == 0 ? g.N / 128 : 0;
 }
 int pt_gemm_mfma_ksplit(const pt_gemm_args& g) {
   if (!pt_gemm_mfma_covers(g) || g.epi != EPI_RESIDUAL || g.M > 256 || g.blk_group || !g.sk_part) return 1;
@@ -147,7 +171,10 @@ int pt_gemm_skinny_ksplit(const pt_gemm_args& g) {
   while (ks > 1 && ((int64_t)ks * g.batch * g.M * g.N > g.sk_part_floats || g.K % (ks * 512))) --ks;
   return ks;
 }
-bool pt_gemm_fuses_norm(const pt_gemm_args& g) { return skinny_ok(g) && g.M <= 4 && (g.epi == EPI_QKV || g.epi == EPI_SWIGLU) && g.lda == g.K; }
+bool pt_gemm_fuses_norm(const pt_gemm_args& g) {
+  if (g.dtype == PT_F32) return pt_gemm_generic_fuses_norm(g);
+  return skinny_ok(g) && g.M <= 4 && (g.epi == EPI_QKV || g.epi == EPI_SWIGLU) && g.lda == g.K;
+}
 int pt_launch_gemm_skinny(const pt_gemm_args& g_in, bool allow_split, hipStream_t) {
   pt_gemm_args g = g_in;
   if (g.n_groups > 0) {
