@@ -48,11 +48,12 @@ static bool cfg_fits(const pt_gemm_args& g, int cfg) {
 // rounds of one tile per compute unit, each with an epilogue and a part per K step of 64, both longer the more of the chip
 // works (`full`); the tiles of 2 share their unit two at a time.  Fitted inside the Mid model (4 tracks, K = 1024 and 4096;
 // us, measured 0 / 2): gate/up 100 rows 30 / 20, 512 33 / 42, 600 50 / 50, 1000 56 / 73, 4096 202 / 271; QKV 512 30 / 27, 1000
-// 36 / 41, 1300 58 / 51, 4096 88 / 125; out 1000 39 / 22, 3000 50 / 51, 4096 56 / 68; down 1000 84 / 46, 2000 93 / 76, 4096
-// 114 / 155; head 300 41 / 44, 1000 72 / 98.  It orders them correctly there and for Large (8 tracks, 512 rows: gate/up
-// 188 / 282, out 61 / 55) and the one-GPU share (512 rows: gate/up 325 / 441, down 484 / 281).  4 wins where one round of it
-// takes a residual GEMM that leaves 0 half empty and fills 2 twice (Mid down 1300 rows 65 against 84 / 75, Large down 512
-// 137 against 171 / 170) and for QKV of few rows with heads of 128, too wide for a wavefront of 2 (Large 96 rows 51 / 57).
+// 36 / 41, 1300 58 / 51, 4096 88 / 125; out 1000 33 / 20, 3000 47 / 49, 4096 57 / 65; down 1000 77 / 44, 2000 83 / 73, 4096
+// 113 / 150; head 300 41 / 44, 1000 72 / 98; the residual terms were fitted on an epilogue that took 1 to 7 us longer).  It
+// orders them correctly there but for down around 1500 rows (4 takes 65 of its 70) and for Large (8 tracks, 512 rows: gate/up
+// 195 / 282, out 62 / 53) and the one-GPU share (512 rows: gate/up 325 / 440, down 476 / 278).  4 wins where one round of it
+// takes a residual GEMM that leaves 0 half empty and fills 2 twice (Mid down 1300 rows 59 against 76 / 71, Large down 512
+// 139 against 171 / 164) and for QKV of few rows with heads of 128, too wide for a wavefront of 2 (Large 96 rows 48 / 56).
 static double tile_us(const pt_gemm_args& g, int cfg) {
   const int bm = cfg == 0 ? 256 : 128, bn = cfg == 2 ? 128 : 256;
   const int64_t tiles = (int64_t)((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn) * g.batch;
