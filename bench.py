@@ -404,7 +404,8 @@ def run_cpu_baseline(I):
 def run_tile_clocks(torch):
     """Where the time of a 256 x 256 tile of the prefill GEMM goes at the Large shapes (libpt_ceilings.so,
     pt_gemm_tile_clocks: the forward library's tile kernel compiled from the same source with shader-clock
-    stamps): entry to first MFMA, K loop, barrier, epilogue, per wavefront, averaged over the launch."""
+    stamps): begin of the tile to its first MFMA, K loop, wait for the last products, epilogue, per wavefront, averaged
+    over the launch."""
     import ctypes as C
     path = os.path.join(ROOT, "paper_2602_07306_amd", "libpt_ceilings.so")
     if not os.path.exists(path):
@@ -442,12 +443,12 @@ def run_tile_clocks(torch):
         ms = r[9]
         rec = {"gemm": name, "M": M, "N": N, "K": K, "batch": T, "ms_per_launch": ms,
                "TFLOPs": 2.0 * M * N * K * T / (ms * 1e-3) / 1e12,
-               "clocks": {"entry_to_first_mfma": r[0], "k_loop": r[1], "barrier": r[2], "epilogue": r[3], "tile": r[4]},
+               "clocks": {"begin_to_first_mfma": r[0], "k_loop": r[1], "wait_for_products": r[2], "epilogue": r[3], "tile": r[4]},
                "tile_us": r[5] / 1e3, "shader_clock_GHz": r[4] / r[5], "stamped_launch_span_ms": r[6] / 1e6,
                "tiles": int(r[7]), "tiles_per_cu": r[7] / 256.0, "k_loop_clocks_at_mfma_rate": 2.0 * 256 * 256 * K / 4069.0}
         out.append(rec)
         log("%s: %.2f ms/launch (%.0f TFLOP/s); per tile %.1f k clocks = first MFMA after %.1f k + K loop %.1f k "
-            "(%.1f k at the MFMA rate) + barrier %.1f k + epilogue %.1f k; clock %.2f GHz"
+            "(%.1f k at the MFMA rate) + wait %.1f k + epilogue %.1f k; clock %.2f GHz"
             % (name, ms, rec["TFLOPs"], r[4] / 1e3, r[0] / 1e3, r[1] / 1e3, rec["k_loop_clocks_at_mfma_rate"] / 1e3,
                r[2] / 1e3, r[3] / 1e3, rec["shader_clock_GHz"]))
         del a, w, o, stamps, rf, ob, gain, sums
@@ -456,9 +457,10 @@ def run_tile_clocks(torch):
 
 
 def run_ceilings(torch, I):
-    """Sustained rates of bare loops on this GPU (libpt_ceilings.so, include/pt_ceilings.h): the matrix-core loop
-    on all-zero operands and on operands distributed like the model's (N(0,1) activations against N(0,0.02)
-    weights), a streaming read, a streaming copy and an LDS read loop.  Context for the roofline fractions: the
+    """Sustained rates of bare loops on this GPU (libpt_ceilings.so, include/pt_ceilings.h): the matrix-core loops of
+    both instruction shapes on all-zero operands and on operands distributed like the model's (N(0,1) activations
+    against N(0,0.02) weights), a streaming read, a streaming copy and an LDS read loop; and a large product of torch's
+    GEMM library on the same two kinds of operand.  Context for the roofline fractions: the
     published peaks are what a kernel is priced against, these are what the chip holds under load."""
     import ctypes as C
     import numpy as np
@@ -467,7 +469,7 @@ def run_ceilings(torch, I):
         raise ImportError("%s is missing: build it with `python -m paper_2602_07306_amd.build`" % path)
     L = C.CDLL(path)
     vp, i32, dbl = C.c_void_p, C.c_int32, C.c_double
-    L.pt_ceiling_mfma_bf16.argtypes = [vp, vp, i32, i32, i32, vp, C.POINTER(dbl)]
+    L.pt_ceiling_mfma_bf16.argtypes = L.pt_ceiling_mfma16_bf16.argtypes = [vp, vp, i32, i32, i32, vp, C.POINTER(dbl)]
     L.pt_ceiling_hbm_read.argtypes = [vp, C.c_size_t, vp, i32, vp, C.POINTER(dbl)]
     L.pt_ceiling_hbm_copy.argtypes = [vp, vp, C.c_size_t, i32, vp, C.POINTER(dbl)]
     L.pt_ceiling_lds_read.argtypes = [vp, i32, i32, i32, vp, dbl, C.POINTER(dbl), C.POINTER(dbl)]
@@ -483,12 +485,32 @@ def run_ceilings(torch, I):
         if rc != 0:
             raise RuntimeError("libpt_ceilings call failed with %d" % rc)
 
-    for name, buf in ops.items():
-        for wps in (1, 2):
-            v = dbl()
-            check(L.pt_ceiling_mfma_bf16(buf.data_ptr(), sink.data_ptr(), wps, 40000, 5, st, C.byref(v)))
-            out["mfma_bf16_TFLOPs"]["%s, %d wavefront(s) per SIMD" % (name, wps)] = v.value
-            log("MFMA loop, %s, %d wavefront(s) per SIMD: %.0f TFLOP/s" % (name, wps, v.value))
+    for shape, loop, iters in (("32x32x16", L.pt_ceiling_mfma_bf16, 40000), ("16x16x32", L.pt_ceiling_mfma16_bf16, 20000)):
+        for name, buf in ops.items():
+            for wps in (1, 2):
+                v = dbl()
+                check(loop(buf.data_ptr(), sink.data_ptr(), wps, iters, 5, st, C.byref(v)))
+                out["mfma_bf16_TFLOPs"]["%s, %s, %d wavefront(s) per SIMD" % (shape, name, wps)] = v.value
+                log("MFMA loop %s, %s, %d wavefront(s) per SIMD: %.0f TFLOP/s" % (shape, name, wps, v.value))
+    out["library_product_TFLOPs"] = {}
+    m, n, k = 4096, 57344, 8192
+    for name, sd in (("zeros", 0.0), ("model-like (N(0,1) x N(0,0.02))", 0.02)):
+        gen = torch.Generator(device="cuda")
+        gen.manual_seed(12)
+        a = torch.randn((m, k), generator=gen, device="cuda").mul_(1.0 if sd else 0.0).to(torch.bfloat16)
+        w = torch.randn((n, k), generator=gen, device="cuda").mul_(sd).to(torch.bfloat16)
+        o = torch.empty((m, n), dtype=torch.bfloat16, device="cuda")
+        for _ in range(3):
+            torch.mm(a, w.t(), out=o)
+        e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        e0.record()
+        for _ in range(20):
+            torch.mm(a, w.t(), out=o)
+        e1.record()
+        torch.cuda.synchronize()
+        out["library_product_TFLOPs"]["%d x %d x %d, %s" % (m, n, k, name)] = 2.0 * m * n * k * 20 / e0.elapsed_time(e1) / 1e9
+        log("library product, %s: %.0f TFLOP/s" % (name, out["library_product_TFLOPs"]["%d x %d x %d, %s" % (m, n, k, name)]))
+        del a, w, o
     nbytes = 8 << 30
     src = torch.ones(nbytes // 4, dtype=torch.float32, device="cuda")
     dst = torch.empty_like(src)

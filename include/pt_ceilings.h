@@ -25,6 +25,11 @@ extern "C" {
 int pt_ceiling_mfma_bf16(const void* dev_operands, void* dev_sink, int32_t waves_per_simd, int32_t iters,
                          int32_t reps, void* hip_stream, double* tflops);
 
+/* The same with v_mfma_f32_16x16x32_bf16 on 16x16 accumulator tiles, 64 (one wavefront per SIMD) or 32 (two) of
+ * them per wavefront: the instruction and the registers of the square GEMM tiles.  2*16*16*32 FLOPs each. */
+int pt_ceiling_mfma16_bf16(const void* dev_operands, void* dev_sink, int32_t waves_per_simd, int32_t iters,
+                           int32_t reps, void* hip_stream, double* tflops);
+
 /* Streaming read of `bytes` (a multiple of 1 MiB) from dev_src with 16-byte loads, every byte once;
  * dev_sink: at least 4 MiB.  Grids of 4 to 64 workgroups per compute unit are tried; *gbs receives the best
  * bytes / time in GB/s. */
@@ -48,8 +53,9 @@ int pt_ceiling_lds_read(void* dev_sink, int32_t waves_per_simd, int32_t iters, i
  * (bf16 [batch][M][N/2] into dev_out).  Optional: dev_row_factor (float [batch][M], SwiGLU: the folded RMSNorm factor),
  * dev_out_bf16 / dev_gain / dev_row_sums (residual: the folded RMSNorm outputs, bf16 [batch][M][N], float
  * [batch][N], float [batch][M][N/128]); all three or none.  dev_stamps: scratch of at least tiles * 4 * 8 * 8 bytes.
- * Three unstamped launches are timed first.  out10: mean shader clocks of entry to first MFMA, K loop, barrier
- * behind it, epilogue, whole tile; then the tile's time in ns, the launch's span in ns, tiles, wavefronts that left
+ * Three unstamped launches are timed first.  A workgroup takes one tile after the other, and the first K steps of a
+ * tile are loaded during the last ones of the tile before, so a tile begins where its predecessor's epilogue ends.
+ * out10: mean shader clocks of a tile's begin to its first MFMA, K loop, wait for the last MFMAs, epilogue, whole tile; then the tile's time in ns, the launch's span in ns, tiles, wavefronts that left
  * stamps, and ms per unstamped launch.  Allocates a host buffer for the stamps only. */
 int pt_gemm_tile_clocks(int32_t epilogue, const void* dev_a, const void* dev_w, void* dev_out, void* dev_out_bf16,
                         const float* dev_row_factor, const float* dev_gain, float* dev_row_sums, int32_t M, int32_t N,

@@ -9,6 +9,7 @@
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8_t;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16_t;
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
 #define CEIL_CHECK(expr) do { if ((expr) != hipSuccess) return -6; } while (0)
@@ -90,6 +91,66 @@ extern "C" int pt_ceiling_mfma_bf16(const void* dev_operands, void* dev_sink, in
   if (rc) return rc;
   const double per_wave = waves_per_simd == 1 ? 2.0 * 16 : 2.0 * 8;   // instructions per iteration
   *tflops = (double)cus * 4 * waves_per_simd * iters * per_wave * 32768.0 / (ms * 1e-3) / 1e12;
+  return 0;
+}
+
+// The same with 16x16x32 instructions, MI x NI tiles of them: as many accumulators, written and read half as often per
+// operation.  In inline assembly, as in the square GEMM tiles: the compiler would copy the accumulators between registers.
+template <int MI, int NI>
+__global__ void __launch_bounds__(MI == 8 ? 256 : 512) mfma16_loop_kernel(const u32x4_t* __restrict__ src, float* __restrict__ out, int iters) {
+#if defined(__HIP_DEVICE_COMPILE__)   // the register class exists on the device only
+  const int tid = threadIdx.x + blockIdx.x * blockDim.x;
+  union { u32x4_t u; bf16x8_t v; } a[2][MI], b[2][NI];   // entries 0-3 of every eight feed a, 4-7 b
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+#pragma unroll
+    for (int i = 0; i < MI; ++i) a[s][i].u = src[(size_t)((tid * 4 + s * 2 + i / 4) * 8 + i % 4) & 0xfffff];
+#pragma unroll
+    for (int i = 0; i < NI; ++i) b[s][i].u = src[(size_t)((tid * 4 + s * 2 + i / 4) * 8 + 4 + i % 4) & 0xfffff];
+  }
+  f32x4_t acc[MI][NI];
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int j = 0; j < NI; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  for (int it = 0; it < iters; ++it) {
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NI; ++j) {
+          const int y = (i & 1) ? NI - 1 - j : j;   // back and forth: one operand changes at a time
+          asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc[i][y]) : "v"(a[s][i].v), "v"(b[s][y].v));
+        }
+  }
+  asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");   // the last results arrive; the compiler does not see the instructions
+  float sum = 0.f;
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int j = 0; j < NI; ++j) {
+      asm volatile("" : "+a"(acc[i][j]));
+      sum += acc[i][j].x + acc[i][j].y + acc[i][j].z + acc[i][j].w;
+    }
+  out[tid & 0xfffff] = sum;
+#endif
+}
+
+extern "C" int pt_ceiling_mfma16_bf16(const void* dev_operands, void* dev_sink, int32_t waves_per_simd, int32_t iters,
+                                      int32_t reps, void* hip_stream, double* tflops) {
+  if (!dev_operands || !dev_sink || !tflops || iters < 1 || reps < 1 || (waves_per_simd != 1 && waves_per_simd != 2)) return -7;
+  hipStream_t st = (hipStream_t)hip_stream;
+  const int cus = device_cus();
+  double ms = 0;
+  int rc;
+  if (waves_per_simd == 1)
+    rc = timed([&] { hipLaunchKernelGGL((mfma16_loop_kernel<8, 8>), dim3(cus), dim3(256), 0, st, (const u32x4_t*)dev_operands, (float*)dev_sink, iters); }, reps, st, &ms);
+  else
+    rc = timed([&] { hipLaunchKernelGGL((mfma16_loop_kernel<4, 8>), dim3(cus), dim3(512), 0, st, (const u32x4_t*)dev_operands, (float*)dev_sink, iters); }, reps, st, &ms);
+  if (rc) return rc;
+  const double per_wave = waves_per_simd == 1 ? 2.0 * 64 : 2.0 * 32;   // instructions per iteration
+  *tflops = (double)cus * 4 * waves_per_simd * iters * per_wave * 16384.0 / (ms * 1e-3) / 1e12;
   return 0;
 }
 

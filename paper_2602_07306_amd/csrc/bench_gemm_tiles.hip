@@ -1,6 +1,6 @@
 // libpt_ceilings.so, second part: the prefill GEMM's 256 x 256 tile kernel compiled from the product source with
-// phase stamps (PT_GEMM_STAMPS), so that the time of a tile can be split into pipeline fill, K loop, barrier and
-// epilogue on the real kernel (include/pt_ceilings.h, bench.py --tile-clocks).  Benchmark-only translation unit.
+// phase stamps (PT_GEMM_STAMPS), so that the time of a tile can be split into its begin (row factors, place of the next
+// tile), K loop, wait for the last products and epilogue on the real kernel (include/pt_ceilings.h, bench.py --tile-clocks).  Benchmark-only translation unit.
 #include <stdarg.h>
 #include <stdio.h>
 #include <string.h>
@@ -107,9 +107,9 @@ extern "C" int pt_gemm_tile_clocks(int32_t epilogue, const void* dev_a, const vo
     ++n;
   }
   if (!n) return -6;
-  out10[0] = d[0] / n;            // entry to first MFMA, shader clocks
+  out10[0] = d[0] / n;            // begin of the tile to its first MFMA, shader clocks
   out10[1] = d[1] / n;            // K loop
-  out10[2] = d[2] / n;            // barrier behind the K loop
+  out10[2] = d[2] / n;            // wait for the last products
   out10[3] = d[3] / n;            // epilogue
   out10[4] = total / n;           // whole tile
   out10[5] = wall / n * 10.0;     // whole tile, ns (100 MHz counter)

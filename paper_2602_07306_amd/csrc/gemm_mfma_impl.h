@@ -123,8 +123,9 @@ __device__ __forceinline__ tile_coord map_tile(int id, int total, int tiles_m, i
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 // Instrumented build (the tile-clock benchmark only): every wavefront of gemm_mfma_kernel leaves shader-clock
-// stamps of its phases in pt_gemm_stamps[(workgroup * 4 + wavefront) * 8 + i]; i = 0 entry, 1 first MFMA, 2 end of
-// the K loop, 3 past the barrier, 4 end of the epilogue; 6 and 7 the constant 100 MHz counter at entry and exit.
+// stamps of its phases in pt_gemm_stamps[(tile * 4 + wavefront) * 8 + i]; i = 0 entry, 1 first MFMA, 2 end of
+// the K loop, 3 past the barrier (persistent tiles: the wait for the last products), 4 end of the epilogue; 6 and 7 the
+// constant 100 MHz counter at entry and exit.
 #ifdef PT_GEMM_STAMPS
 __device__ long long* pt_gemm_stamps = nullptr;
 #define PT_STAMP_TILE(tile, i)                                                                                         \
