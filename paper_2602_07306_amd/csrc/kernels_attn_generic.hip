@@ -12,9 +12,11 @@ __device__ __forceinline__ float4 load4(const bf16_t* p) {
 // VEC: four elements per load, the loads of a key row (and of 16 keys of V^T) in flight together, and two groups of
 // keys side by side where a head is at most 32 wide (hd % 4 == 0, pointers aligned).  The loop of single loads waits
 // for memory once per key: one row of the Tiny model (32 to 40 keys, head width 32) 8.6 us before, 5.3 now.
-// NARROW (VEC, heads of at most 32): what bounds it is one load's latency after the other, so a chunk's keys, its values
-// and q are requested together.
-template <typename T, bool VEC, bool NARROW>
+// NARROW (VEC, heads of at most 32; the number of loads of a key's row, 4 up to 16 elements, else 8): what bounds it is one
+// load's latency after the other, so a chunk's keys, its values and q are requested together.  Eight loads also of narrower
+// rows repeat the last one: two prompts of 1024 tokens, 8 tracks, 16 heads of 16, the whole pass in ms, no form of its own /
+// eight loads / four: 12.0 / 12.7 / 10.8.
+template <typename T, bool VEC, int NARROW>
 __global__ void __launch_bounds__(64) attn_generic_kernel(pt_attn_args a) {
   __shared__ __attribute__((aligned(16))) float qs[256];
   const int lane = threadIdx.x;
@@ -50,7 +52,7 @@ __global__ void __launch_bounds__(64) attn_generic_kernel(pt_attn_args a) {
     const int key = base + lane;
     float s = -INFINITY;
     const int nk = min(64, nkeys - base);
-    float4 kv[NARROW ? 8 : 1], vv[NARROW ? 8 : 1];
+    float4 kv[NARROW ? NARROW : 1], vv[NARROW ? 8 : 1];
     (void)kv; (void)vv;
     if constexpr (NARROW) {
       // lane: head-dim index lane % 32 of the values at positions 8 i + 4 * (lane / 32) .. + 3; the 64 positions of a chunk
@@ -58,7 +60,7 @@ __global__ void __launch_bounds__(64) attn_generic_kernel(pt_attn_args a) {
       const T* kr = K + (int64_t)min(key, nkeys - 1) * hd;
       const T* vr = Vt + (int64_t)min(lane & 31, hd - 1) * a.s_pad + base + 4 * (lane >> 5);
 #pragma unroll
-      for (int i = 0; i < 8; ++i) kv[i] = load4(kr + min(4 * i, hd - 4));
+      for (int i = 0; i < NARROW; ++i) kv[i] = load4(kr + min(4 * i, hd - 4));
 #pragma unroll
       for (int i = 0; i < 8; ++i)
         if (8 * i < nk) vv[i] = load4(vr + 8 * i);
@@ -68,7 +70,7 @@ __global__ void __launch_bounds__(64) attn_generic_kernel(pt_attn_args a) {
       }
       float4 d = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
-      for (int i = 0; i < 8; ++i)
+      for (int i = 0; i < NARROW; ++i)
         if (4 * i < hd) {
           const float4 q4 = *(const float4*)(qs + 4 * i);
           d.x = fmaf(q4.x, kv[i].x, d.x); d.y = fmaf(q4.y, kv[i].y, d.y); d.z = fmaf(q4.z, kv[i].z, d.z); d.w = fmaf(q4.w, kv[i].w, d.w);
@@ -152,15 +154,17 @@ int pt_launch_attn_generic(const pt_attn_args& a, hipStream_t s) {
   if (a.hd > 256) return pt_set_error(PT_ERR_INVALID_ARGUMENT, "head_dim > 256");
   dim3 grid((unsigned)rows, (unsigned)a.H, (unsigned)a.n_tracks);
   const bool vec = !((a.hd | a.s_pad) & 3) && !(a.kv_head_elems & 3) && !(((uintptr_t)a.kc | (uintptr_t)a.vc) & 15);
-  if (a.dtype == PT_F32) {
-    if (vec && a.hd <= 32) hipLaunchKernelGGL((attn_generic_kernel<float, true, true>), grid, dim3(64), 0, s, a);
-    else if (vec) hipLaunchKernelGGL((attn_generic_kernel<float, true, false>), grid, dim3(64), 0, s, a);
-    else hipLaunchKernelGGL((attn_generic_kernel<float, false, false>), grid, dim3(64), 0, s, a);
-  } else {
-    if (vec && a.hd <= 32) hipLaunchKernelGGL((attn_generic_kernel<bf16_t, true, true>), grid, dim3(64), 0, s, a);
-    else if (vec) hipLaunchKernelGGL((attn_generic_kernel<bf16_t, true, false>), grid, dim3(64), 0, s, a);
-    else hipLaunchKernelGGL((attn_generic_kernel<bf16_t, false, false>), grid, dim3(64), 0, s, a);
-  }
+  const int narrow = !vec || a.hd > 32 ? 0 : a.hd > 16 ? 8 : 4;
+  auto launch = [&](auto kern) { hipLaunchKernelGGL(kern, grid, dim3(64), 0, s, a); };
+  auto of_type = [&](auto t) {
+    using T = decltype(t);
+    if (narrow == 4) launch(attn_generic_kernel<T, true, 4>);
+    else if (narrow == 8) launch(attn_generic_kernel<T, true, 8>);
+    else if (vec) launch(attn_generic_kernel<T, true, 0>);
+    else launch(attn_generic_kernel<T, false, 0>);
+  };
+  if (a.dtype == PT_F32) of_type(float{});
+  else of_type(bf16_t{});
   PT_HIP_CHECK(hipGetLastError());
   return PT_OK;
 }

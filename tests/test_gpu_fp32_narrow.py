@@ -12,7 +12,7 @@ torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("hd", [8, 24, 32, 40])
+@pytest.mark.parametrize("hd", [8, 16, 24, 32, 40])
 @pytest.mark.parametrize("B,S", [(1, 63), (1, 64), (5, 65), (3, 130)])
 def test_fp32_rows_with_their_own_norm(hd, B, S):
     from paper_2602_07306_amd import binding as PB
