@@ -209,7 +209,13 @@ static bool rows_covers(const pt_gemm_args& g) {
   return !(g.a_bstride & 3) && !((uintptr_t)g.A & 15);
 }
 
-bool pt_gemm_generic_fuses_norm(const pt_gemm_args& g) { return rows_covers(g) && g.epi != EPI_RESIDUAL; }
+// The norm inside costs every wavefront of several rows about 0.3 ns of the chip, whatever K (sums of squares and their
+// lane sums), the launch it saves 3.8 us.  QKV or gate/up, us with it / without: 4 tracks, width 1024, 4 rows QKV (6144
+// wavefronts) 20.1 / 17.8, 8 rows (12288) 29.6 / 24.9, 4 rows gate/up (16384) 36.5 / 32.0; 1 x 1024, 8 rows gate/up (8192) 20.1 /
+// 16.6; 2 x 2048, 8 rows QKV (12288) 46.3 / 42.0, 24 rows (36864) 95 / 82; a layer of the last 291 / 271.  One row: 27.5 / 27.1 at 16384.
+bool pt_gemm_generic_fuses_norm(const pt_gemm_args& g) {
+  return rows_covers(g) && g.epi != EPI_RESIDUAL && (g.M == 1 || (int64_t)(g.N / 2) * ((g.M + 3) / 4) * g.batch < 12288);
+}
 
 int pt_launch_gemm_generic(const pt_gemm_args& g, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0 || g.batch <= 0) return PT_OK;
